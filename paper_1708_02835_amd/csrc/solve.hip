@@ -17,10 +17,11 @@
 
 namespace gl {
 
-// v_k <- L_kk⁻¹ v_k by 64-row blocks J, using the inverted diagonal blocks
-// D_J⁻¹ that POTRF left in `dinv`:  t = v_J - L[J, 0:J] w[0:J],  w_J = D_J⁻¹ t.
-// Both products are split over four thread groups with fixed-order partial
-// sums.  The tile's part of wᵀw (rows < n) goes to quad_part[k].
+// v_k <- L_kk⁻¹ v_k by 128-row blocks, using the inverted 64×64 diagonal
+// blocks D⁻¹ that POTRF left in `dinv`: in each, w_0 = D_0⁻¹ v_0 and
+// w_1 = D_1⁻¹ (v_1 - L_10 w_0), then the rows below take -L w.  Every product
+// is split over four thread groups with fixed-order partial sums.  The tile's
+// part of wᵀw (rows < n) goes to quad_part[k], summed by 128-row blocks.
 template <int B>
 __device__ __forceinline__ void fwd_diag_body(const double *__restrict__ tiles, int64_t k, int64_t n,
                                               double *__restrict__ v, double *__restrict__ quad_part,
@@ -37,35 +38,53 @@ __device__ __forceinline__ void fwd_diag_body(const double *__restrict__ tiles, 
     const int r = tid & 63, g = tid >> 6;
     __shared__ double xs[B];
     __shared__ double t[64];
-    __shared__ double part[4][64];
+    __shared__ double part[4][B];
     __shared__ double red[4];
     for (int q = tid; q < B; q += 256) xs[q] = vk[q];
     __syncthreads();
     for (int J = 0; J < B; J += 64) {
-        double acc = 0.0;
-        for (int c = g; c < J; c += 4) acc += L[(int64_t)c * B + J + r] * xs[c];
-        part[g][r] = acc;
-        __syncthreads();
-        if (tid < 64) t[r] = xs[J + r] - ((part[0][r] + part[1][r]) + (part[2][r] + part[3][r]));
+        const bool second = J & 64;
+        if (second) {
+            double acc = 0.0;
+            for (int c = J - 64 + g; c < J; c += 4) acc = fma(L[(int64_t)c * B + J + r], xs[c], acc);
+            part[g][r] = acc;
+            __syncthreads();
+        }
+        if (tid < 64)
+            t[r] = second ? xs[J + r] - ((part[0][r] + part[1][r]) + (part[2][r] + part[3][r])) : xs[J + r];
         __syncthreads();
         const double *dv = dinv + (int64_t)(J / 64) * 64 * 64;
-        acc = 0.0;
-        for (int m = g; m < 64; m += 4) acc += dv[m * 64 + r] * t[m];
+        double acc = 0.0;
+        for (int m = g; m < 64; m += 4) acc = fma(dv[m * 64 + r], t[m], acc);
         part[g][r] = acc;
         __syncthreads();
         if (tid < 64) xs[J + r] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
         __syncthreads();
+        if (second && J + 64 < B) {
+            // rows below the 128-row block
+            for (int R = J + 64; R < B; R += 64) {
+                acc = 0.0;
+#pragma unroll 8
+                for (int c = J - 64 + g; c < J + 64; c += 4) acc = fma(L[(int64_t)c * B + R + r], xs[c], acc);
+                part[g][R + r] = acc;
+            }
+            __syncthreads();
+            for (int R = J + 64 + tid; R < B; R += 256)
+                xs[R] -= (part[0][R] + part[1][R]) + (part[2][R] + part[3][R]);
+            __syncthreads();
+        }
     }
-    double q = 0.0;
-    for (int rr = tid; rr < B; rr += 256) {
-        vk[rr] = xs[rr];
-        if (k * B + rr < n) q += xs[rr] * xs[rr];
-    }
+    for (int rr = tid; rr < B; rr += 256) vk[rr] = xs[rr];
     if (quad_part) {
-        double w = wave_sum(q);
-        if (lane == 0) red[wave] = w;
-        __syncthreads();
-        if (tid == 0) quad_part[k] = (red[0] + red[1]) + (red[2] + red[3]);
+        double total = 0.0;
+        for (int s = 0; s < B; s += 128) {
+            const double w = wave_sum(tid < 128 && k * B + s + tid < n ? xs[s + tid] * xs[s + tid] : 0.0);
+            __syncthreads();
+            if (lane == 0) red[wave] = w;
+            __syncthreads();
+            total += (red[0] + red[1]) + (red[2] + red[3]);
+        }
+        if (tid == 0) quad_part[k] = total;
     }
 }
 
@@ -79,7 +98,8 @@ __global__ __launch_bounds__(256) void fwd_diag_kernel(const double *__restrict_
     fwd_diag_body<B>(tiles, k, n, v, quad_part, dinv, info);
 }
 
-// v_i -= L_ik v_k for every tile i > k; workgroup (tile i = k + 1 + tix, 64-row strip).
+// v_i -= L_ik v_k for every tile i > k, one 128-column block of L_ik after the
+// other; workgroup (tile i = k + 1 + tix, 64-row strip).
 template <int B>
 __device__ __forceinline__ void fwd_update_body(const double *__restrict__ tiles, int64_t k,
                                                 double *__restrict__ v, const int64_t *__restrict__ info,
@@ -92,15 +112,24 @@ __device__ __forceinline__ void fwd_update_body(const double *__restrict__ tiles
     const double *L = tiles + tile_offset(i, k, B);
     const int tid = threadIdx.x;
     __shared__ double wk[B];
-    __shared__ double red[4][64];
+    __shared__ double red[B / 128][4][64];
     for (int c = tid; c < B; c += 256) wk[c] = v[k * B + c];
     __syncthreads();
     const int r = tid & 63, g = tid >> 6;
-    double acc = 0.0;
-    for (int c = g; c < B; c += 4) acc += L[(int64_t)c * B + r0 + r] * wk[c];
-    red[g][r] = acc;
+#pragma unroll
+    for (int s = 0; s < B / 128; ++s) {
+        double acc = 0.0;
+#pragma unroll 8
+        for (int c = 128 * s + g; c < 128 * s + 128; c += 4) acc = fma(L[(int64_t)c * B + r0 + r], wk[c], acc);
+        red[s][g][r] = acc;
+    }
     __syncthreads();
-    if (g == 0) v[i * B + r0 + r] -= (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
+    if (g == 0) {
+        double x = v[i * B + r0 + r];
+#pragma unroll
+        for (int s = 0; s < B / 128; ++s) x -= (red[s][0][r] + red[s][1][r]) + (red[s][2][r] + red[s][3][r]);
+        v[i * B + r0 + r] = x;
+    }
 }
 
 template <int B>

@@ -4,7 +4,7 @@
 // Workgroup (i, strip) owns 64 rows of tile (i, k), the only writer of those
 // rows, and solves them in place in 64-column blocks J, all on the matrix
 // cores:
-//   T      = A[:, J] - X[:, 0:J] · L_kk[J, 0:J]ᵀ
+//   -T     = -A[:, J] + X[:, 0:J] · L_kk[J, 0:J]ᵀ  (one accumulation, like the trailing update)
 //   X[:, J] = T · D_J⁻ᵀ
 // where D_J⁻¹ is the inverse of the J-th 64×64 diagonal block of L_kk, left in
 // `dinv` by the POTRF of the same step.  The product streams 16-column chunks
@@ -29,7 +29,7 @@ __device__ __forceinline__ void trsm_core(const double *__restrict__ L, double *
     const int r0 = strip * TB;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // chunk buffers during the product (Xs[b][kc][r] = X[r0 + r][k0 + kc],
     // Ls[b][kc][j] = L[J + j][k0 + kc]); D_J⁻¹ reuses them afterwards
     __shared__ double buf[2 * TC * TP * 2];
@@ -42,9 +42,13 @@ __device__ __forceinline__ void trsm_core(const double *__restrict__ L, double *
 
     for (int J = 0; J < B; J += TB) {
         const int nch = J / TC;
+        // result row q of lane l: block column w*16 + l/16 + 4q, lane % 16: strip row
         d4 acc[4];
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) acc[rb] = (d4){0.0, 0.0, 0.0, 0.0};
+        for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[rb][q] = -X[(int64_t)(J + wave * 16 + mfma_row(lane, q)) * B + r0 + rb * 16 + mfma_col(lane)];
         d2 rx[2], rl[2];
         if (nch > 0) {
             const d2 *px = reinterpret_cast<const d2 *>(X + (int64_t)lkc * B + r0 + lr);
@@ -86,29 +90,32 @@ __device__ __forceinline__ void trsm_core(const double *__restrict__ L, double *
             }
             __syncthreads();
         }
-        // T = A[:, J] - product (result row q of lane l: block column w*16 + l/16 + 4q,
-        // lane % 16: strip row), and D_J⁻¹ into LDS
+        // T and D_J⁻¹ into LDS
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int c = wave * 16 + mfma_row(lane, q);
                 const int r = rb * 16 + mfma_col(lane);
-                Tt[c][r] = X[(int64_t)(J + c) * B + r0 + r] - acc[rb][q];
+                Tt[c][r] = -acc[rb][q];
             }
         const double *dv = dinv + (int64_t)(J / TB) * TB * TB;
         for (int e = tid; e < TB * TB; e += 256) Di[(e >> 6) * TP + (e & 63)] = dv[e];
         __syncthreads();
-        // X[:, J] = T · D_J⁻ᵀ: X[r][c] = Σ_m T[r][m] D⁻¹[c][m]
+        // X[:, J] = T · D_J⁻ᵀ: X[r][c] = Σ_{m <= c} T[r][m] D⁻¹[c][m]
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb) acc[rb] = (d4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int kk = 0; kk < TB; kk += 4) {
-            const int m = kk + (lane >> 4);
-            const double xd = Di[m * TP + wave * 16 + (lane & 15)];
+        for (int kb = 0; kb < 4; ++kb)
+            if (kb <= wave) {
 #pragma unroll
-            for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_f64(xd, Tt[m][rb * 16 + (lane & 15)], acc[rb]);
-        }
+                for (int kk = 16 * kb; kk < 16 * kb + 16; kk += 4) {
+                    const int m = kk + (lane >> 4);
+                    const double xd = Di[m * TP + wave * 16 + (lane & 15)];
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_f64(xd, Tt[m][rb * 16 + (lane & 15)], acc[rb]);
+                }
+            }
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
