@@ -297,6 +297,13 @@ int factorize(Lanes &ln, Work &w, hipStream_t s, bool solve, int64_t near, bool 
     return solve ? solve_join(ln, s) : GL_OK;
 }
 
+int factor_fp64(Lanes &ln, Work &w, hipStream_t s, bool solve, int32_t near_tiles)
+{
+    const bool flow = flow_factorize && !ln.prof && near_tiles == 0;
+    if (flow) return flow_factorize(w, s, solve);
+    return factorize(ln, w, s, solve, near_tiles_for(w.b, near_tiles));
+}
+
 int solve_step(Lanes &ln, Work &w, int64_t k, hipStream_t s)
 {
     GL_HIP_TRY(hipEventRecord(ln.ready, s));
@@ -490,7 +497,7 @@ int eval_launch(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream_t s
     if (o.precision == GL_FP64) {
         timed(ln.prof, GL_PHASE_GEN, 0.0, s,
               [&] { launch_gen_tiles(w.tiles, w.x, w.y, w.n, w.b, w.nt, th, geom_of(o), nullptr, s); });
-        rc = factorize(ln, w, s, true, near_tiles_for(w.b, o.near_tiles));
+        rc = factor_fp64(ln, w, s, true, o.near_tiles);
     } else {
         rc = mixed_factorize(ln, w, th, o, s, plan_out);
     }
@@ -587,7 +594,7 @@ static int graph_eval(gl_context *ctx, Work &w, const double *x, const double *y
         GL_HIP_TRY(hipStreamBeginCapture(g, hipStreamCaptureModeThreadLocal));
         launch_fill(reinterpret_cast<double *>(w.info), 1, 0.0, g);
         launch_gen_tiles_dev(w.tiles, w.x, w.y, w.n, w.b, w.nt, ctx->theta_d, geo, g);
-        int rc = factorize(ln, w, g, true, near);
+        int rc = factor_fp64(ln, w, g, true, o.near_tiles);
         launch_final_reduce(w.logsum, w.quad, w.nt, w.n, w.info, w.res, g);
         hipGraph_t graph = nullptr;
         const hipError_t ec = hipStreamEndCapture(g, &graph);
@@ -943,7 +950,7 @@ int synth_generate(gl_context *ctx, const double *x, const double *y, const doub
     launch_copy_pad(e, n, w.v, w.npad, 0.0, s);
     launch_fill(reinterpret_cast<double *>(w.info), 1, 0.0, s);
     launch_gen_tiles(w.tiles, w.x, w.y, w.n, w.b, w.nt, th, geom_of(o), nullptr, s);
-    rc = factorize(ctx->lanes, w, s, false, near_tiles_for(w.b, o.near_tiles));
+    rc = factor_fp64(ctx->lanes, w, s, false, o.near_tiles);
     if (rc != GL_OK) return rc;
     // z = L e: e is read from v, the padded product goes to the x buffer (no
     // longer needed once the tiles exist), then its first n values to z

@@ -118,6 +118,13 @@ bool valid_theta_for(const gl_theta &t, const gl_opts &o);
 size_t work_bytes(int64_t n, int b, int precision);
 // first_done: the POTRF of tile 0 has already run (logsum[0], dinv of step 0).
 int factorize(Lanes &ln, Work &w, hipStream_t s, bool solve, int64_t near, bool first_done = false);
+// The same in one launch (flow.hip): every block of L computed start to end by
+// one workgroup, the same operations in the same order, so the same bits as
+// factorize().  Not part of builds without device code (weak).
+int flow_factorize(Work &w, hipStream_t s, bool solve) __attribute__((weak));
+// Factorisation of a binary64 evaluation by whichever of the two applies;
+// near_tiles as in gl_opts.
+int factor_fp64(Lanes &ln, Work &w, hipStream_t s, bool solve, int32_t near_tiles);
 // Forward solve of step k (diagonal block and the update of the rows below)
 // on ln.sv once the work queued on s so far (column k final) is done; the
 // caller has made ln.sv wait for the inputs.  solve_join makes s wait for

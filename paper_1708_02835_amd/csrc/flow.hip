@@ -1,0 +1,523 @@
+// The whole tiled Cholesky factorisation and forward solve (Alg. 2 steps 3-6)
+// in one launch.
+//
+// The matrix is cut into 128×128 blocks (a storage tile of b = 128 s holds s×s
+// of them).  One task computes one block of L from start to end, left-looking:
+//   block (i, j), i > j:  -T = -A_ij + Σ_{k<j} L_ik L_jkᵀ,  L_ij = T L_jj⁻ᵀ,
+//                         v_i -= L_ij w_j
+//   block (j, j):         the same sum, its Cholesky factor, the inverses of its
+//                         two 64×64 diagonal blocks, w_j = L_jj⁻¹ v_j and the
+//                         block's parts of log|Σ| and wᵀw
+// with the accumulators of the sum in registers throughout, so a block of A is
+// read once and a block of L written once whatever the number of panels (the
+// step schedule reads and writes it once per one or two panels), and nothing
+// waits at a kernel boundary: a block starts its sum as soon as its first
+// panels exist and follows the frontier.
+//
+// Workgroups take tasks from a ticket counter in column order, diagonal block
+// first.  Every task depends only on tasks with smaller tickets, and a ticket
+// is only held by a running workgroup, so the smallest unfinished task can
+// always proceed: no co-residency of the grid is assumed, and every wait ends.
+// Progress words (agent-scope, release after the data, acquire before its
+// use): prog[i] = blocks of row i that are final (row i's blocks finish in
+// column order, since each needs the one before), ready[j] = 1 once L_jj's
+// first 64 columns and D_0⁻¹ are final, 2 with the second half, 3 with w_j.
+// A pivot that is not positive stores its column in *info; workgroups that
+// wait see it and leave.
+//
+// Four waves of 32 rows × 128 columns: a wave then holds whole rows of T, and
+// since a 16x16x4 result has the lane layout of a B operand, the triangular
+// solve of its rows runs from registers, without an exchange.  The diagonal
+// block gives wave w the 16-row blocks w and 7 - w, nine of the 36 lower
+// blocks each.
+//
+// The sequence of operations on every element is that of the step schedule
+// (potrf.hip, trsm.hip, trailing.hip, solve.hip), so both give the same bits.
+#include <algorithm>
+
+#include "common.hpp"
+#include "engine.hpp"
+#include "mfma.hpp"
+#include "potrf64.hpp"
+
+namespace gl {
+
+namespace {
+
+constexpr int FB = 128;      // block edge
+constexpr int FK = 16;       // columns per staged chunk
+constexpr int FP = FB + 16;  // LDS pitch of a staged chunk (bank spread, as trailing.hip)
+constexpr int FC = FB / FK;  // chunks per block
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+struct FlowProb {
+    double *tiles, *v, *dinv, *logsum, *quad;
+    int64_t *info;
+    int *words;   // ticket, then prog and ready, `stride` ints apart
+    int64_t n;
+    int nb, pad;  // blocks with rows below n; all-padding blocks after them
+    int stride, solve;
+};
+
+struct FlowShared {
+    double buf[4 * FK * FP];  // K loop: two chunks of both operands
+    double v[FB], w[FB];
+    double part[4][PB];
+    double red[4];
+    int fail, word;
+};
+
+__device__ __forceinline__ int peek(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void post(int *p, int x) { __hip_atomic_store(p, x, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Waits until min(*a, *b) >= want and returns it; -1 when the factorisation
+// has failed.  Called by every thread; one polls.
+__device__ __forceinline__ int await(const int *a, const int *b, int want, const int64_t *info, FlowShared &sh)
+{
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int x;
+        while ((x = min(peek(a), peek(b))) < want) {
+            if (__hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                x = -1;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        sh.word = x;
+    }
+    __syncthreads();
+    return sh.word;
+}
+
+// Every wave's stores so far are in the cache of its XCD when this returns;
+// the release of the thread that posts a progress word then publishes them.
+__device__ __forceinline__ void settle()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// The thread index as a value the compiler knows nothing about: addresses
+// derived from it are computed where they are used, not once outside the task
+// loop and spilled.
+__device__ __forceinline__ int thread_index()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// 64×64 column-major block (ld) to LDS, column m's row c at m·64 + (c ^ 16 (m & 1)):
+// the two 16-lane halves of an operand read fall in different banks.
+__device__ __forceinline__ void stage64(const double *__restrict__ src, int64_t ld, double *dst)
+{
+    const int tid = thread_index();
+    d2 r[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int e = 2 * tid + 512 * q;
+        r[q] = *reinterpret_cast<const d2 *>(src + (e >> 6) * ld + (e & 63));
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int e = 2 * tid + 512 * q;
+        *reinterpret_cast<d2 *>(dst + (e & ~63) + ((e & 63) ^ ((e >> 2) & 16))) = r[q];
+    }
+}
+__device__ __forceinline__ double staged(const double *s, int m, int c) { return s[m * 64 + (c ^ ((m & 1) << 4))]; }
+
+// acc += rows of A times rows of B over the columns [c0, c1) (multiples of
+// FK), A and B 128 rows of ld B.  DIAG: A == B, and wave w's two row blocks
+// are w and 7 - w, columns up to the diagonal only.
+template <int B, bool DIAG>
+__device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const double *__restrict__ Bp, int c0, int c1,
+                                           d4 (&acc)[2][8], double *buf)
+{
+    auto As = reinterpret_cast<double(*)[FK][FP]>(buf);
+    auto Bs = reinterpret_cast<double(*)[FK][FP]>(buf + 2 * FK * FP);
+    const int tid = thread_index();
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = tid >> 4;
+    const int le = (tid & 15) * 2;
+    const int ra0 = DIAG ? wave * 16 : wave * 32, ra1 = DIAG ? (7 - wave) * 16 : wave * 32 + 16;
+    d2 ra[4], rb[4];
+    auto load = [&](int col) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ra[q] = *reinterpret_cast<const d2 *>(Ap + (int64_t)(col + lc) * B + le + 32 * q);
+            if constexpr (!DIAG) rb[q] = *reinterpret_cast<const d2 *>(Bp + (int64_t)(col + lc) * B + le + 32 * q);
+        }
+    };
+    auto store = [&](int cur) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            *reinterpret_cast<d2 *>(&As[cur][lc][le + 32 * q]) = ra[q];
+            if constexpr (!DIAG) *reinterpret_cast<d2 *>(&Bs[cur][lc][le + 32 * q]) = rb[q];
+        }
+    };
+    load(c0);
+    store(0);
+    __syncthreads();
+    int cur = 0;
+    for (int c = c0; c < c1; c += FK, cur ^= 1) {
+        if (c + FK < c1) load(c + FK);
+#pragma unroll
+        for (int kk = 0; kk < FK; kk += 4) {
+            const double *arow = As[cur][kk + (lane >> 4)];
+            const double *brow = DIAG ? arow : Bs[cur][kk + (lane >> 4)];
+            const double a0 = arow[ra0 + (lane & 15)], a1 = arow[ra1 + (lane & 15)];
+            double bv[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) bv[b] = brow[b * 16 + (lane & 15)];
+            // operands swapped: result row = block column, lane % 16 = block row
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                if (!DIAG || (b < 4 && b <= wave)) acc[0][b] = mfma_f64(bv[b], a0, acc[0][b]);
+                if (!DIAG || b < 4 || b <= 7 - wave) acc[1][b] = mfma_f64(bv[b], a1, acc[1][b]);
+            }
+        }
+        // the staging of the next chunk stays after this chunk's products
+        __builtin_amdgcn_sched_barrier(0);
+        if (c + FK < c1) store(cur ^ 1);
+        __syncthreads();
+    }
+}
+
+// X = T D⁻ᵀ for 16-row groups held as -T in acc[.][h .. h+3] (in place), D⁻¹
+// lower triangular, read by inv(m, c) = D⁻¹[c][m].
+template <int NA, int H, class F>
+__device__ __forceinline__ void solve64(d4 (*acc)[8], F &&inv)
+{
+    const int lane = thread_index() & 63;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][H + b] = -acc[a][H + b];
+#pragma unroll
+    for (int cb = 3; cb >= 0; --cb) {
+        d4 x[NA];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) x[a] = (d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int mb = 0; mb <= cb; ++mb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double dv = inv(16 * mb + 4 * r + (lane >> 4), 16 * cb + (lane & 15));
+#pragma unroll
+                for (int a = 0; a < NA; ++a) x[a] = mfma_f64(dv, acc[a][H + mb][r], x[a]);
+            }
+#pragma unroll
+        for (int a = 0; a < NA; ++a) acc[a][H + cb] = x[a];
+    }
+}
+
+// Block (i, j), i > j.  False when the factorisation has failed.
+template <int B>
+__device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowShared &sh)
+{
+    constexpr int S = B / FB;
+    const int tid = thread_index();
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // row panels: column c of rows 128 i .. at rows(i) + c·B
+    const double *Ai = p.tiles + tile_offset(i / S, 0, B) + (i % S) * FB;
+    const double *Bj = p.tiles + tile_offset(j / S, 0, B) + (j % S) * FB;
+    double *C = const_cast<double *>(Ai) + (int64_t)j * FB * B;
+    const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(C, (short)0, FB * B * 8, 0x00020000);
+    const int cvo = (mfma_row(lane, 0) * B + wave * 32 + mfma_col(lane)) * 8;
+    int *prog = p.words + 2 * p.stride, *ready = prog + p.nb * p.stride;
+
+    d4 acc[2][8];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc[a][b][r] = -__builtin_bit_cast(
+                    double, __builtin_amdgcn_raw_buffer_load_b64(crs, cvo, ((b * 16 + 4 * r) * B + a * 16) * 8, 0));
+    for (int k = 0; k < j;) {
+        const int have = await(prog + i * p.stride, prog + j * p.stride, k + 1, p.info, sh);
+        if (have < 0) return false;
+        const int e = min(have, j);
+        accumulate<B, false>(Ai, Bj, k * FB, e * FB, acc, sh.buf);
+        k = e;
+    }
+    // first 64 columns, then the second
+    const double *Ljj = Bj + (int64_t)j * FB * B;
+    const double *dv = p.dinv + (int64_t)j * 2 * PB * PB;
+    double *s0 = sh.buf, *s1 = sh.buf + PB * PB;
+    if (await(ready + j * p.stride, ready + j * p.stride, 1, p.info, sh) < 0) return false;
+    stage64(dv, PB, s0);
+    stage64(Ljj + PB, B, s1);
+    __syncthreads();
+    solve64<2, 0>(acc, [&](int m, int c) { return staged(s0, m, c); });
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double l = staged(s1, 16 * mb + 4 * r + (lane >> 4), 16 * cb + (lane & 15));
+#pragma unroll
+                for (int a = 0; a < 2; ++a) acc[a][4 + cb] = mfma_f64(l, acc[a][mb][r], acc[a][4 + cb]);
+            }
+    auto put = [&](int h) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = h; b < h + 4; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double x = acc[a][b][r];
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), crs, cvo,
+                                                          ((b * 16 + 4 * r) * B + a * 16) * 8, 0);
+                }
+    };
+    put(0);
+    if (await(ready + j * p.stride, ready + j * p.stride, 2, p.info, sh) < 0) return false;
+    stage64(dv + PB * PB, PB, s0);
+    __syncthreads();
+    solve64<2, 4>(acc, [&](int m, int c) { return staged(s0, m, c); });
+    put(4);
+    if (p.solve) {
+        if (await(ready + j * p.stride, ready + j * p.stride, 3, p.info, sh) < 0) return false;
+        if (tid < FB) sh.w[tid] = p.v[(int64_t)j * FB + tid];
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            double s = 0.0;
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s = fma(acc[a][b][r], sh.w[b * 16 + mfma_row(lane, r)], s);
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (lane < 16) p.v[(int64_t)i * FB + wave * 32 + a * 16 + lane] -= s;
+        }
+    }
+    settle();
+    if (tid == 0) post(prog + i * p.stride, j + 1);
+    return true;
+}
+
+// Block (j, j).  False when the factorisation fails or has failed.
+template <int B>
+__device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &sh)
+{
+    constexpr int S = B / FB;
+    const int tid = thread_index();
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const double *Aj = p.tiles + tile_offset(j / S, 0, B) + (j % S) * FB;
+    double *C = const_cast<double *>(Aj) + (int64_t)j * FB * B;
+    double *vj = p.v + (int64_t)j * FB;
+    double *dv = p.dinv + (int64_t)j * 2 * PB * PB;
+    int *prog = p.words + 2 * p.stride, *ready = prog + (p.nb + j) * p.stride;
+    const int64_t rows = p.n - (int64_t)j * FB;  // rows that are not padding
+    const int q = lane >> 4, r16 = lane & 15;
+    const int rb0 = wave, rb1 = 7 - wave;  // 16-row blocks of this wave
+
+    d4 acc[2][8];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc[a][b][r] = -C[(int64_t)(b * 16 + mfma_row(lane, r)) * B + (a ? rb1 : rb0) * 16 + r16];
+    for (int k = 0; k < j;) {
+        const int have = await(prog + j * p.stride, prog + j * p.stride, k + 1, p.info, sh);
+        if (have < 0) return false;
+        const int e = min(have, j);
+        accumulate<B, true>(Aj, Aj, k * FB, e * FB, acc, sh.buf);
+        k = e;
+    }
+    auto X = reinterpret_cast<double(*)[PB + 1]>(sh.buf);                  // D_0, then X_10, then D_1⁻¹
+    auto Y = reinterpret_cast<double(*)[PB + 1]>(sh.buf + PB * (PB + 1));  // D_0⁻¹, then D_1
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+        if (b <= wave) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) X[b * 16 + mfma_row(lane, r)][rb0 * 16 + r16] = -acc[0][b][r];
+        }
+    if (tid < FB) sh.v[tid] = vj[tid];
+    if (tid == 0) sh.fail = 0;
+    __syncthreads();
+    if (!factor_invert_64(X, Y, &sh.fail, (int64_t)j * FB, p.info)) {
+        if (tid == 0) __threadfence();
+        return false;
+    }
+    // L_00 and D_0⁻¹ out, the rows below by 16-row blocks, one per wave
+    for (int e = tid; e < PB * PB; e += 256) {
+        const int c = e >> 6, r = e & 63;
+        if (r >= c) C[(int64_t)c * B + r] = X[c][r];
+        dv[e] = r >= c ? Y[c][r] : 0.0;
+    }
+    solve64<1, 0>(&acc[1], [&](int m, int c) { return Y[m][c]; });
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) C[(int64_t)(b * 16 + mfma_row(lane, r)) * B + rb1 * 16 + r16] = acc[1][b][r];
+    // w_0 = D_0⁻¹ v_0
+    const int vr = tid & 63, vg = tid >> 6;
+    if (p.solve) {
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < PB; m += 4) s = fma(m + vg <= vr ? Y[m + vg][vr] : 0.0, sh.v[m + vg], s);
+        sh.part[vg][vr] = s;
+    }
+    double lg = wave == 0 && lane < rows ? log(X[lane][lane]) : 0.0;
+    settle();
+    if (tid == 192) post(ready, 1);
+    if (p.solve && tid < PB) sh.w[vr] = (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]);
+    // X_10 to LDS, -D_1 += X_10 X_10ᵀ
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) X[b * 16 + mfma_row(lane, r)][(3 - wave) * 16 + r16] = acc[1][b][r];
+    __syncthreads();
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+        if (cb <= 3 - wave) {
+#pragma unroll
+            for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc[1][4 + cb] = mfma_f64(X[16 * mb + 4 * r + q][16 * cb + r16], acc[1][mb][r], acc[1][4 + cb]);
+        }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+        if (cb <= 3 - wave) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Y[16 * cb + mfma_row(lane, r)][(3 - wave) * 16 + r16] = -acc[1][4 + cb][r];
+        }
+    if (p.solve) {
+        // v_1 - L_10 w_0
+        double s = 0.0;
+#pragma unroll
+        for (int c = 0; c < PB; c += 4) s = fma(X[c + vg][vr], sh.w[c + vg], s);
+        sh.part[vg][vr] = s;
+    }
+    __syncthreads();
+    if (p.solve && tid < PB) sh.v[PB + vr] -= (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]);
+    if (!factor_invert_64(Y, X, &sh.fail, (int64_t)j * FB + PB, p.info)) {
+        if (tid == 0) __threadfence();
+        return false;
+    }
+    for (int e = tid; e < PB * PB; e += 256) {
+        const int c = e >> 6, r = e & 63;
+        if (r >= c) C[(int64_t)(PB + c) * B + PB + r] = Y[c][r];
+        dv[PB * PB + e] = r >= c ? X[c][r] : 0.0;
+    }
+    settle();
+    if (tid == 192) post(ready, 2);
+    if (wave == 1) lg = PB + lane < rows ? log(Y[lane][lane]) : 0.0;
+    if (p.solve) {
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < PB; m += 4) s = fma(m + vg <= vr ? X[m + vg][vr] : 0.0, sh.v[PB + m + vg], s);
+        sh.part[vg][vr] = s;
+        __syncthreads();
+        if (tid < PB) sh.w[PB + vr] = (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]);
+        __syncthreads();
+        const double w = tid < FB ? sh.w[tid] : 0.0;
+        if (tid < FB) vj[tid] = w;
+        // the block's parts, added in block order (the storage tile's first block starts the sums)
+        double part = wave_sum(lg);
+        if (lane == 0 && wave < 2) sh.red[wave] = part;
+        part = wave_sum(tid < rows ? w * w : 0.0);
+        if (lane == 0 && wave < 2) sh.red[2 + wave] = part;
+        __syncthreads();
+        if (tid == 0) {
+            const int t = j / S;
+            double ls = 2.0 * (sh.red[0] + sh.red[1]), qs = sh.red[2] + sh.red[3];
+            if (j % S) {
+                ls = p.logsum[t] + ls;
+                qs = p.quad[t] + qs;
+            }
+            p.logsum[t] = ls;
+            p.quad[t] = qs;
+        }
+        settle();
+        if (tid == 0) post(ready, 3);
+    }
+    return true;
+}
+
+template <int B>
+__global__ __launch_bounds__(256, 2) void flow_kernel(FlowProb p)
+{
+    __shared__ FlowShared sh;
+    const int total = p.nb * (p.nb + 1) / 2;
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0)
+            sh.word = __hip_atomic_fetch_add(p.words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        int t = __builtin_amdgcn_readfirstlane(sh.word);
+        if (t >= total + p.pad) return;
+        if (t >= total) {
+            // a diagonal block that is all padding: L is the identity Σ has there
+            double *dv = p.dinv + (int64_t)(p.nb + t - total) * 2 * PB * PB;
+            for (int e = threadIdx.x; e < 2 * PB * PB; e += 256) dv[e] = ((e >> 6) & 63) == (e & 63) ? 1.0 : 0.0;
+            continue;
+        }
+        // column j holds nb - j tasks
+        const double a = 2.0 * p.nb + 1.0;
+        int j = (int)((a - sqrt(a * a - 8.0 * t)) * 0.5);
+        j = max(j, 0);
+        while (j > 0 && j * p.nb - j * (j - 1) / 2 > t) --j;
+        while ((j + 1) * p.nb - (j + 1) * j / 2 <= t) ++j;
+        const int i = j + t - (j * p.nb - j * (j - 1) / 2);
+        bool ok;
+        if (i == j) {
+            __builtin_amdgcn_s_setprio(3);  // the critical chain
+            ok = flow_diag<B>(p, j, sh);
+        } else {
+            if (i == j + 1) __builtin_amdgcn_s_setprio(2);
+            else __builtin_amdgcn_s_setprio(0);
+            ok = flow_off<B>(p, i, j, sh);
+        }
+        if (!ok) return;
+    }
+}
+
+}  // namespace
+
+int flow_factorize(Work &w, hipStream_t s, bool solve)
+{
+    FlowProb p;
+    p.tiles = w.tiles;
+    p.v = w.v;
+    p.dinv = w.dinv;
+    p.logsum = w.logsum;
+    p.quad = w.quad;
+    p.info = w.info;
+    p.n = w.n;
+    p.nb = (int)ceil_div(w.n, FB);
+    p.pad = (int)(w.npad / FB) - p.nb;
+    p.solve = solve;
+    // the words take the place of the sort keys, which the staging is done
+    // with; a cache line each where the keys leave room
+    p.words = reinterpret_cast<int *>(w.keys);
+    p.stride = w.n >= FB ? 16 : 1;
+    const int64_t bytes = (2 + 2 * (int64_t)p.nb) * p.stride * (int64_t)sizeof(int);
+    if (bytes > (npow2_of(w.n) + 4) * (int64_t)sizeof(uint64_t)) return GL_EINVAL;
+    launch_fill(reinterpret_cast<double *>(w.keys), ceil_div(bytes, 8), 0.0, s);
+    const int64_t tasks = (int64_t)p.nb * (p.nb + 1) / 2 + p.pad;
+    const unsigned grid = (unsigned)std::min<int64_t>(tasks, 512);
+    switch (w.b) {
+    case 128: flow_kernel<128><<<grid, 256, 0, s>>>(p); break;
+    case 256: flow_kernel<256><<<grid, 256, 0, s>>>(p); break;
+    case 384: flow_kernel<384><<<grid, 256, 0, s>>>(p); break;
+    default: flow_kernel<512><<<grid, 256, 0, s>>>(p); break;
+    }
+    GL_HIP_TRY(hipGetLastError());
+    return GL_OK;
+}
+
+}  // namespace gl
