@@ -69,8 +69,11 @@ void launch_fwd_diag(const double *tiles, int b, int64_t k, int64_t n, double *v
                      const double *dinv, const int64_t *info, hipStream_t s);
 void launch_fwd_update(const double *tiles, int b, int64_t nt, int64_t k, double *v,
                        const int64_t *info, hipStream_t s);
-void launch_bwd_diag(const double *tiles, int b, int64_t k, double *v, hipStream_t s);
-void launch_bwd_update(const double *tiles, int b, int64_t k, double *v, hipStream_t s);
+// v <- L⁻ᵀ v (back.hip; weak: not part of builds without device code), with
+// BACK_WORDS doubles of scratch
+constexpr int BACK_WORDS = 16;
+void launch_backward(const double *tiles, const double *dinv, int b, int64_t n, double *v, double *words,
+                     hipStream_t s) __attribute__((weak));
 void launch_trmv(const double *tiles, int b, int64_t nt, const double *e, double *z, hipStream_t s);
 void launch_final_reduce(const double *logdet_part, const double *quad_part, int64_t nt, int64_t n,
                          const int64_t *info, DevResult *res, hipStream_t s);

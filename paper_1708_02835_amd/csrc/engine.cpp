@@ -812,21 +812,19 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     const int64_t chunks = var ? std::min<int64_t>(8, ceil_div(m, w.b)) : 0;
     const size_t st_len = (size_t)chunks * w.npad * w.b;
     double *scratch = nullptr;
-    const size_t bytes = ((size_t)w.npad + m * nchunk + st_len + (size_t)chunks * w.npad) * sizeof(double);
+    const size_t bytes =
+        (BACK_WORDS + (size_t)w.npad + m * nchunk + st_len + (size_t)chunks * w.npad) * sizeof(double);
     if (hipMallocAsync(reinterpret_cast<void **>(&scratch), bytes, s) != hipSuccess) {
         (void)hipGetLastError();
         return GL_ENOMEM;
     }
-    double *xv = scratch;
-    double *part = scratch + w.npad;
+    double *xv = scratch + BACK_WORDS;
+    double *part = xv + w.npad;
     double *st = part + m * nchunk;
     double *vpart = st + st_len;
-    // X = L⁻ᵀ w: backward substitution over tile rows, last to first
-    GL_HIP_TRY(hipMemcpyAsync(xv, w.v, (size_t)w.npad * sizeof(double), hipMemcpyDeviceToDevice, s));
-    for (int64_t k = w.nt - 1; k >= 0; --k) {
-        launch_bwd_diag(w.tiles, w.b, k, xv, s);
-        launch_bwd_update(w.tiles, w.b, k, xv, s);
-    }
+    // X = L⁻ᵀ w
+    launch_copy_pad(w.v, w.npad, xv, w.npad, 0.0, s);
+    if (launch_backward) launch_backward(w.tiles, w.dinv, w.b, w.n, xv, scratch, s);
     launch_krige(w.x, w.y, w.n, xv, f->theta, geo, xnew, ynew, m, part, nchunk, s);
     launch_krige_reduce(part, m, nchunk, znew, s);
     // var_k = θ1 - ||L⁻¹ σ_k||², right-hand sides solved on the matrix cores

@@ -50,6 +50,7 @@ struct IndPlan {
     std::vector<int64_t> start, nb, ntb;
     const double *sx = nullptr, *sy = nullptr;
     DevResult *total = nullptr;
+    double *words = nullptr;  // BACK_WORDS doubles
 };
 
 // Enqueues the factorisation of the blocks [start[i], start[i] + count[i])
@@ -62,10 +63,10 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
 {
     const int64_t nblk = (int64_t)start.size();
     const int64_t block = bt * b;  // uniform block length (the likelihood's), for the reported column
-    // layout (in doubles): descriptors | totals | per-block results, info |
+    // layout (in doubles): descriptors | total | solve words | per-block results, info |
     // per block: tiles, x, y, v, logsum, quad, dinv | reordered inputs, keys
     const size_t desc_d = ((size_t)nblk * sizeof(BatchReq) + 15) / 16 * 2;
-    size_t off = desc_d + 8 + 8 * (size_t)nblk + 8 * (size_t)nblk;
+    size_t off = desc_d + 8 + BACK_WORDS + 8 * (size_t)nblk + 8 * (size_t)nblk;
     std::vector<size_t> boff(nblk);
     std::vector<int64_t> nb(nblk), ntb(nblk);
     for (int64_t i = 0; i < nblk; ++i) {
@@ -95,8 +96,9 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
     double *base = static_cast<double *>(ctx->ind_buf);
     BatchReq *ddesc = reinterpret_cast<BatchReq *>(base);
     DevResult *total = reinterpret_cast<DevResult *>(base + desc_d);
-    DevResult *bres = reinterpret_cast<DevResult *>(base + desc_d + 8);
-    int64_t *binfo = reinterpret_cast<int64_t *>(base + desc_d + 8 + 8 * nblk);
+    double *words = base + desc_d + 8;
+    DevResult *bres = reinterpret_cast<DevResult *>(words + BACK_WORDS);
+    int64_t *binfo = reinterpret_cast<int64_t *>(words + BACK_WORDS + 8 * nblk);
     const double *sx = x, *sy = y, *sz = z;
     if (reorder) {
         double *xo = base + morton_off, *yo = xo + n, *zo = yo + n;
@@ -176,6 +178,7 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
     p.sx = sx;
     p.sy = sy;
     p.total = total;
+    p.words = words;
     return GL_OK;
 }
 
@@ -224,10 +227,7 @@ int ind_krige(gl_context *ctx, const double *x, const double *y, const double *z
         // X = L⁻ᵀ w within each block, in place
         for (int64_t i = 0; i < p.nblk; ++i) {
             const BatchReq &d = p.proto[i];
-            for (int64_t k = p.ntb[i] - 1; k >= 0; --k) {
-                launch_bwd_diag(d.tiles, p.b, k, d.v, s);
-                launch_bwd_update(d.tiles, p.b, k, d.v, s);
-            }
+            launch_backward(d.tiles, d.dinv, p.b, d.n, d.v, p.words, s);
         }
     }
     // each block's held-out values from its own observed values

@@ -1,10 +1,9 @@
-// Triangular solves, TRMV and the scalar reductions on the packed tile factor.
+// Forward solve, TRMV and the scalar reductions on the packed tile factor.
 //
 //  * forward solve w = L⁻¹ Z (Alg. 2 step 4, "dtrsm" with one right-hand side),
 //    by tile columns: solve the diagonal block, then subtract L_ik w_k from the
 //    blocks below; the diagonal-block kernel also emits the tile's part of
 //    wᵀw (Alg. 2 step 6);
-//  * backward solve X = L⁻ᵀ w (the second half of "dposv" in Alg. 3);
 //  * Z = L e (Alg. 1 step 7, "dtrmm");
 //  * the final fixed-order reduction of the per-tile log-det and quadratic
 //    form parts into l(θ) (Alg. 2 step 7, Eq. (1)).
@@ -138,74 +137,6 @@ __global__ __launch_bounds__(256) void fwd_update_kernel(const double *__restric
                                                          const int64_t *__restrict__ info)
 {
     fwd_update_body<B>(tiles, k, v, info, blockIdx.x, blockIdx.y);
-}
-
-// v_k <- L_kk⁻ᵀ v_k, 64-row blocks from the bottom: the block's rows first
-// receive the contributions of the solved rows below it (column dot products),
-// then wave 0 back-substitutes the 64×64 block held in LDS.
-template <int B>
-__global__ __launch_bounds__(256) void bwd_diag_kernel(const double *__restrict__ tiles, int64_t k,
-                                                       double *__restrict__ v)
-{
-    const double *L = tiles + tile_offset(k, k, B);
-    double *vk = v + k * B;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    __shared__ double xs[B];
-    __shared__ double Lb[64][65];  // Lb[c][r] = L[s + r][s + c]
-    for (int r = tid; r < B; r += 256) xs[r] = vk[r];
-    __syncthreads();
-    for (int s = B - 64; s >= 0; s -= 64) {
-        // xs[c] -= Σ_{r >= s+64} L[r][c] xs[r] for the 64 columns c of this block
-        for (int cc = wave * 16; cc < wave * 16 + 16; ++cc) {
-            const int c = s + cc;
-            double acc = 0.0;
-            for (int r = s + 64 + lane; r < B; r += 64) acc += L[(int64_t)c * B + r] * xs[r];
-            acc = wave_sum(acc);
-            if (lane == 0) xs[c] -= acc;
-        }
-        for (int e = tid; e < 64 * 64; e += 256) {
-            const int c = e >> 6, r = e & 63;
-            Lb[c][r] = L[(int64_t)(s + c) * B + s + r];
-        }
-        __syncthreads();
-        if (wave == 0) {
-            double z = xs[s + lane];
-            for (int c = 63; c >= 0; --c) {
-                const double xc = __shfl(z, c, 64) / Lb[c][c];
-                if (lane == c) z = xc;
-                else if (lane < c) z -= Lb[lane][c] * xc;  // L[s + c][s + lane]
-            }
-            xs[s + lane] = z;
-        }
-        __syncthreads();
-    }
-    for (int r = tid; r < B; r += 256) vk[r] = xs[r];
-}
-
-// v_j -= L_kjᵀ v_k for every tile j < k; workgroup (j, 64-column strip),
-// each wave 16 columns, one column dot product at a time.
-template <int B>
-__global__ __launch_bounds__(256) void bwd_update_kernel(const double *__restrict__ tiles, int64_t k,
-                                                         double *__restrict__ v)
-{
-    const int64_t j = blockIdx.x;
-    const int c0 = blockIdx.y * 64;
-    const double *L = tiles + tile_offset(k, j, B);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    __shared__ double xk[B];
-    for (int r = tid; r < B; r += 256) xk[r] = v[k * B + r];
-    __syncthreads();
-    for (int cc = wave * 16; cc < wave * 16 + 16; ++cc) {
-        const int c = c0 + cc;
-        double acc = 0.0;
-        for (int r = lane; r < B; r += 64) acc += L[(int64_t)c * B + r] * xk[r];
-        acc = wave_sum(acc);
-        if (lane == 0) v[j * B + c] -= acc;
-    }
 }
 
 // z_i = Σ_{j<i} L_ij e_j + tril(L_ii) e_i; workgroup (i, 64-row strip).
@@ -387,18 +318,6 @@ void launch_fwd_update(const double *tiles, int b, int64_t nt, int64_t k, double
     if (nt - k - 1 <= 0) return;
     dim3 grid((unsigned)(nt - k - 1), (unsigned)(b / 64));
     GL_DISPATCH_B(b, fwd_update_kernel, grid, tiles, k, v, info);
-}
-
-void launch_bwd_diag(const double *tiles, int b, int64_t k, double *v, hipStream_t s)
-{
-    GL_DISPATCH_B(b, bwd_diag_kernel, dim3(1), tiles, k, v);
-}
-
-void launch_bwd_update(const double *tiles, int b, int64_t k, double *v, hipStream_t s)
-{
-    if (k <= 0) return;
-    dim3 grid((unsigned)k, (unsigned)(b / 64));
-    GL_DISPATCH_B(b, bwd_update_kernel, grid, tiles, k, v);
 }
 
 void launch_trmv(const double *tiles, int b, int64_t nt, const double *e, double *z, hipStream_t s)

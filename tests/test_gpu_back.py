@@ -1,0 +1,40 @@
+"""The one-launch backward solve (back.hip) behind kriging, against the oracle:
+sizes around one column block (half a block, a block, a block plus one), ragged
+last tiles of every storage tile size with all-padding blocks, and a chain of
+many blocks.  The bound is that of the kriging parity tests, 1e-9 of the largest
+measurement, far above the rounding of either side (κ(Σ) is below 1e4 here, so
+a solve is good to about 1e-12)."""
+import numpy as np
+import pytest
+
+import geoinputs
+import oracle
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+@pytest.mark.parametrize("n,tile", [(1, 128), (64, 128), (65, 256), (127, 384), (128, 128), (129, 128), (129, 512),
+                                    (385, 256), (641, 512), (900, 384), (1601, 128)])
+def test_backward_solve_through_kriging(n, tile):
+    import paper_1708_02835_amd as g
+    theta = (1.3, 0.1, 0.5)
+    x, y = geoinputs.jittered_grid(n, 8)
+    z = geoinputs.normal_vector(n, 8)
+    xn, yn = geoinputs.uniform_points(33, 8)
+    print(f"back n={n} tile={tile}", flush=True)
+    with g.Context(0) as ctx:
+        r = g.loglik_eval(ctx, dev(x), dev(y), dev(z), theta, g.gl_opts_default(tile=tile, keep_factor=1))
+        assert r["status"] == g.GL_OK
+        first = g.krige_predict(ctx, r["factor"], dev(xn), dev(yn))
+        again = g.krige_predict(ctx, r["factor"], dev(xn), dev(yn))
+        assert torch.equal(first, again)
+        got = first.cpu().numpy()
+        g.gl_factor_release(ctx, r["factor"])
+    want, info = oracle.krige(x, y, z, xn, yn, theta)
+    assert info == 0
+    assert np.max(np.abs(got - want)) <= 1e-9 * np.max(np.abs(z))
