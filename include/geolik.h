@@ -329,8 +329,8 @@ typedef struct {
                                 when its first request arrives (the fused launches use
                                 two streams of their own) */
     int32_t batch_small;     /* 1: FP64 requests with n <= small_n (tile 0 or 256, no
-                                reordering) advance together through fused launches,
-                                one factorisation step per launch, tile 256 */
+                                reordering) run together in fused launches, the whole
+                                evaluations of a batch per launch, tile 256 */
     int32_t small_n;         /* size limit of the fused path */
     size_t hbm_budget_bytes; /* admission budget for resident work (0 = the context's) */
 } lq_config;

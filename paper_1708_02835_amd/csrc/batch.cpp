@@ -1,51 +1,54 @@
-// One step of many independent tiled factorisations in fused launches (see
+// Whole evaluations of many independent problems in fused launches (see
 // batch.hpp): fills the prefix offsets of the descriptors, copies them to the
 // device and enqueues the launches.
+#include <algorithm>
+
 #include "batch.hpp"
 
 namespace gl {
 
-int enqueue_step(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, int *launches)
+int enqueue_whole(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, int *launches)
 {
-    int64_t o_stage = 0, o_gen = 0, o_trsm = 0, o_tr = 0;
-    const int64_t sub = (int64_t)(b / 128) * (b / 128);
-    bool any_new = false, any_fin = false, euclid = true;
+    std::sort(d, d + count, [](const BatchReq &x, const BatchReq &y) { return x.n > y.n; });
+    int64_t o_stage = 0, o_gen = 0, o_flow = 0, pads = 0;
+    bool euclid = true;
     for (int i = 0; i < count; ++i) {
         BatchReq &q = d[i];
+        const int64_t nb = ceil_div(q.n, 128);
+        const int64_t next = i + 1 < count ? ceil_div(d[i + 1].n, 128) : 0;
+        q.is_new = q.finishing = 1;
         q.o_stage = o_stage;
         q.o_gen = o_gen;
-        q.o_trsm = o_trsm;
-        q.o_tr = o_tr;
-        if (q.is_new) {
-            o_stage += ceil_div(q.npad, 256);
-            o_gen += tile_count(q.nt);
-            any_new = true;
-            euclid = euclid && q.geo.metric == GL_EUCLIDEAN;
-        }
-        const int64_t m = q.nt - q.k - 1;
-        o_trsm += m * (b / 64);
-        o_tr += m * (m + 1) / 2 * sub;
-        any_fin = any_fin || q.finishing;
+        q.o_flow = o_flow;
+        o_stage += ceil_div(q.npad, 256);
+        o_gen += tile_count(q.nt);
+        // columns with nb .. next + 1 blocks left, in i + 1 factorisations each
+        o_flow += (i + 1) * (tile_count(nb) - tile_count(next));
+        pads += q.npad / 128 - nb;
+        euclid = euclid && q.geo.metric == GL_EUCLIDEAN;
     }
+    if (o_flow + pads > INT32_MAX) return GL_EINVAL;
     GL_HIP_TRY(hipMemcpyAsync(dev, d, count * sizeof(BatchReq), hipMemcpyHostToDevice, s));
-    int n = 0;
-    if (any_new) {
-        launch_stage_batched(dev, count, o_stage, s);
-        launch_gen_batched(b, dev, count, o_gen, euclid, s);
-        n += 2;
+    launch_stage_batched(dev, count, o_stage, s);
+    launch_gen_batched(b, dev, count, o_gen, euclid, s);
+    if (launch_flow_batched) {
+        launch_flow_batched(b, dev, count, o_flow, pads, s);
+    } else {
+        for (int i = 0; i < count; ++i) {
+            const BatchReq &q = d[i];
+            for (int64_t k = 0; k < q.nt; ++k) {
+                double *dinv = q.dinv + k * 64 * b;
+                launch_potrf(q.tiles, b, k, q.n, q.info, q.logsum, dinv, s);
+                launch_trsm(q.tiles, b, q.nt, k, dinv, q.info, s);
+                launch_fwd_diag(q.tiles, b, k, q.n, q.v, q.quad, dinv, q.info, s);
+                launch_fwd_update(q.tiles, b, q.nt, k, q.v, q.info, s);
+                launch_trailing(q.tiles, b, q.nt, k, k + 1, q.nt - 1, q.info, false, false, s);
+            }
+        }
     }
-    launch_potrf_batched(b, dev, count, s);
-    launch_fwd_diag_batched(b, dev, count, s);
-    launch_trsm_batched(b, dev, count, o_trsm, s);
-    launch_fwd_update_batched(b, dev, count, o_trsm, s);
-    launch_trailing_batched(b, dev, count, o_tr, s);
-    n += 5;
-    if (any_fin) {
-        launch_final_batched(dev, count, s);
-        ++n;
-    }
+    launch_final_batched(dev, count, s);
     GL_HIP_TRY(hipGetLastError());
-    if (launches) *launches = n;
+    if (launches) *launches = 4;
     return GL_OK;
 }
 

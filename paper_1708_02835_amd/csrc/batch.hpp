@@ -1,8 +1,8 @@
-// Descriptors of the fused multi-request launches used by the serving loop.
-// One launch covers the same step of many resident requests; each request's
-// work is a contiguous range of the launch's workgroups, given by exclusive
-// prefix offsets, and runs the same per-request code as a single evaluation,
-// so a request's arithmetic does not depend on what else is in the launch.
+// Descriptors of the fused multi-request launches used by the serving loop and
+// the independent-blocks approximation.  One launch covers the same phase of
+// many requests; each request's work is given by exclusive prefix offsets and
+// runs the same per-request code as a single evaluation, so a request's
+// arithmetic does not depend on what else is in the launch.
 #pragma once
 
 #include "common.hpp"
@@ -16,10 +16,17 @@ struct BatchReq {
     const double *sx, *sy, *sz;  // dataset (sources of the staging copy)
     gl_theta th;
     Geom geo;
-    int64_t n, nt, npad, k;      // k: the step this launch performs
-    int64_t o_stage, o_gen, o_trsm, o_tr;
-    int32_t is_new, finishing;
+    int64_t n, nt, npad, k;      // k: unused by the whole-evaluation launches (0)
+    int64_t o_stage, o_gen, o_flow;
+    int32_t is_new, finishing;   // generates / reduces in this launch (1)
+    int32_t stride;              // of the progress words, in ints
+    int32_t *words;              // flow_words() ints, cleared with the staging
 };
+
+// Progress words of one whole factorisation (flow.hip): a ticket and two words
+// per 128-column block, each on a cache line of its own from one block on.
+__host__ __device__ inline int flow_stride(int64_t n) { return n >= 128 ? 16 : 1; }
+__host__ __device__ inline int64_t flow_words(int64_t n, int stride) { return (2 + 2 * ((n + 127) / 128)) * stride; }
 
 // Largest request index r with offset(r) <= g (ranges may be empty).
 #define GL_BATCH_FIND(d, count, g, field)                    \
@@ -35,18 +42,20 @@ struct BatchReq {
 void launch_stage_batched(const BatchReq *d, int count, int64_t blocks, hipStream_t s);
 // euclid: every request that generates in this launch uses the Euclidean distance.
 void launch_gen_batched(int b, const BatchReq *d, int count, int64_t tiles, bool euclid, hipStream_t s);
-void launch_potrf_batched(int b, const BatchReq *d, int count, hipStream_t s);
-void launch_fwd_diag_batched(int b, const BatchReq *d, int count, hipStream_t s);
-void launch_trsm_batched(int b, const BatchReq *d, int count, int64_t blocks, hipStream_t s);
-void launch_fwd_update_batched(int b, const BatchReq *d, int count, int64_t blocks, hipStream_t s);
-void launch_trailing_batched(int b, const BatchReq *d, int count, int64_t blocks, hipStream_t s);
+// Factorisations and forward solves of all requests, sorted by falling size:
+// `blocks` 128×128 blocks in all and `pads` all-padding diagonal blocks (flow.hip; weak: not
+// part of builds without device code).
+void launch_flow_batched(int b, const BatchReq *d, int count, int64_t blocks, int64_t pads, hipStream_t s)
+    __attribute__((weak));
 void launch_final_batched(const BatchReq *d, int count, hipStream_t s);
 
-// One step for d[0..count): the caller sets every field but the offsets
-// (k, is_new and finishing included); the offsets are filled in, the array is
-// copied to dev (device, count entries) on s and the fused launches follow.
-// d must stay valid until the copy has been consumed (pinned memory: until
-// the stream passes it).
-int enqueue_step(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, int *launches);
+// The whole evaluations of d[0..count) (count >= 1): staging and Σ generation,
+// the factorisations and forward solves, the final sums.  The caller sets
+// the fields up to k, words and stride, with dinv that of step 0; d is sorted
+// and its offsets filled in, the array is copied to dev (device, count
+// entries) on s and the launches follow.  d must stay valid until the copy
+// has been consumed (pinned memory: until the stream passes it).  Builds
+// without device code run the factorisations one after the other by steps.
+int enqueue_whole(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, int *launches);
 
 }  // namespace gl

@@ -35,6 +35,7 @@
 // (potrf.hip, trsm.hip, trailing.hip, solve.hip), so both give the same bits.
 #include <algorithm>
 
+#include "batch.hpp"
 #include "common.hpp"
 #include "engine.hpp"
 #include "mfma.hpp"
@@ -448,41 +449,126 @@ __device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &
     return true;
 }
 
+// Block column j of a factorisation of m block columns and the row's offset
+// below the diagonal, from its index u in column order (column c: m - c blocks).
+__device__ __forceinline__ int flow_column(int u, int m, int &below)
+{
+    const double a = 2.0 * m + 1.0;
+    int j = (int)((a - sqrt(a * a - 8.0 * u)) * 0.5);
+    j = max(j, 0);
+    while (j > 0 && j * m - j * (j - 1) / 2 > u) --j;
+    while ((j + 1) * m - (j + 1) * j / 2 <= u) ++j;
+    below = u - (j * m - j * (j - 1) / 2);
+    return j;
+}
+
+template <int B>
+__device__ __forceinline__ bool flow_task(const FlowProb &p, int i, int j, FlowShared &sh)
+{
+    if (i == j) {
+        __builtin_amdgcn_s_setprio(3);  // the critical chain
+        return flow_diag<B>(p, j, sh);
+    }
+    if (i == j + 1) __builtin_amdgcn_s_setprio(2);
+    else __builtin_amdgcn_s_setprio(0);
+    return flow_off<B>(p, i, j, sh);
+}
+
+// A diagonal block that is all padding: L is the identity Σ has there.
+__device__ __forceinline__ void flow_pad(double *dinv, int j)
+{
+    double *dv = dinv + (int64_t)j * 2 * PB * PB;
+    for (int e = threadIdx.x; e < 2 * PB * PB; e += 256) dv[e] = ((e >> 6) & 63) == (e & 63) ? 1.0 : 0.0;
+}
+
+__device__ __forceinline__ int flow_ticket(int *counter, FlowShared &sh)
+{
+    __syncthreads();
+    if (threadIdx.x == 0)
+        sh.word = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh.word);
+}
+
 template <int B>
 __global__ __launch_bounds__(256, 2) void flow_kernel(FlowProb p)
 {
     __shared__ FlowShared sh;
     const int total = p.nb * (p.nb + 1) / 2;
     for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0)
-            sh.word = __hip_atomic_fetch_add(p.words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        int t = __builtin_amdgcn_readfirstlane(sh.word);
+        const int t = flow_ticket(p.words, sh);
         if (t >= total + p.pad) return;
         if (t >= total) {
-            // a diagonal block that is all padding: L is the identity Σ has there
-            double *dv = p.dinv + (int64_t)(p.nb + t - total) * 2 * PB * PB;
-            for (int e = threadIdx.x; e < 2 * PB * PB; e += 256) dv[e] = ((e >> 6) & 63) == (e & 63) ? 1.0 : 0.0;
+            flow_pad(p.dinv, p.nb + t - total);
             continue;
         }
-        // column j holds nb - j tasks
-        const double a = 2.0 * p.nb + 1.0;
-        int j = (int)((a - sqrt(a * a - 8.0 * t)) * 0.5);
-        j = max(j, 0);
-        while (j > 0 && j * p.nb - j * (j - 1) / 2 > t) --j;
-        while ((j + 1) * p.nb - (j + 1) * j / 2 <= t) ++j;
-        const int i = j + t - (j * p.nb - j * (j - 1) / 2);
-        bool ok;
-        if (i == j) {
-            __builtin_amdgcn_s_setprio(3);  // the critical chain
-            ok = flow_diag<B>(p, j, sh);
-        } else {
-            if (i == j + 1) __builtin_amdgcn_s_setprio(2);
-            else __builtin_amdgcn_s_setprio(0);
-            ok = flow_off<B>(p, i, j, sh);
+        int below;
+        const int j = flow_column(t, p.nb, below);
+        if (!flow_task<B>(p, j + below, j, sh)) return;
+    }
+}
+
+__device__ __forceinline__ FlowProb flow_prob(const BatchReq &q, int S)
+{
+    FlowProb p;
+    p.tiles = q.tiles;
+    p.v = q.v;
+    p.dinv = q.dinv;
+    p.logsum = q.logsum;
+    p.quad = q.quad;
+    p.info = q.info;
+    p.words = q.words;
+    p.n = q.n;
+    p.nb = (int)((q.n + FB - 1) / FB);
+    p.pad = (int)q.nt * S - p.nb;
+    p.stride = q.stride;
+    p.solve = 1;
+    return p;
+}
+
+// Many factorisations, sorted by falling size.  Their columns are aligned at
+// the end (the largest starts alone, the others join when as many columns are
+// left), so the serial tails of all of them run together; a column takes the
+// diagonal blocks of all active factorisations first, then their next blocks.
+// While factorisations 0..a are active every column counts a + 1 times the
+// blocks of the largest, and o_flow of factorisation a is the number of blocks
+// before it joins.
+template <int B>
+__global__ __launch_bounds__(256, 2) void flow_batched_kernel(const BatchReq *__restrict__ d, int count, int total,
+                                                              int pads)
+{
+    __shared__ FlowShared sh;
+    const int lane = threadIdx.x & 63;
+    for (;;) {
+        const int t = flow_ticket(d[0].words, sh);
+        if (t >= total + pads) return;
+        if (t >= total) {
+            int r = t - total;
+            for (int q = 0; q < count; ++q) {
+                const FlowProb p = flow_prob(d[q], B / FB);
+                if (r < p.pad) {
+                    flow_pad(p.dinv, p.nb + r);
+                    break;
+                }
+                r -= p.pad;
+            }
+            continue;
         }
-        if (!ok) return;
+        int active = 0;
+        for (int q0 = 0; q0 < count; q0 += 64) {
+            const int q = q0 + lane;
+            const unsigned long long in = __ballot(q < count && d[min(q, count - 1)].o_flow <= t);
+            active += __popcll(in);
+            if (in != ~0ull) break;
+        }
+        active = __builtin_amdgcn_readfirstlane(active);
+        const BatchReq &last = d[active - 1];
+        const int u = t - (int)last.o_flow;
+        int below;
+        const int c = flow_column(u / active, (int)((last.n + FB - 1) / FB), below);
+        const FlowProb p = flow_prob(d[u % active], B / FB);
+        const int j = c + p.nb - (int)((last.n + FB - 1) / FB);
+        if (!flow_task<B>(p, j + below, j, sh)) return;
     }
 }
 
@@ -504,8 +590,8 @@ int flow_factorize(Work &w, hipStream_t s, bool solve)
     // the words take the place of the sort keys, which the staging is done
     // with; a cache line each where the keys leave room
     p.words = reinterpret_cast<int *>(w.keys);
-    p.stride = w.n >= FB ? 16 : 1;
-    const int64_t bytes = (2 + 2 * (int64_t)p.nb) * p.stride * (int64_t)sizeof(int);
+    p.stride = flow_stride(w.n);
+    const int64_t bytes = flow_words(w.n, p.stride) * (int64_t)sizeof(int);
     if (bytes > (npow2_of(w.n) + 4) * (int64_t)sizeof(uint64_t)) return GL_EINVAL;
     launch_fill(reinterpret_cast<double *>(w.keys), ceil_div(bytes, 8), 0.0, s);
     const int64_t tasks = (int64_t)p.nb * (p.nb + 1) / 2 + p.pad;
@@ -518,6 +604,17 @@ int flow_factorize(Work &w, hipStream_t s, bool solve)
     }
     GL_HIP_TRY(hipGetLastError());
     return GL_OK;
+}
+
+void launch_flow_batched(int b, const BatchReq *d, int count, int64_t blocks, int64_t pads, hipStream_t s)
+{
+    const unsigned grid = (unsigned)std::min<int64_t>(blocks + pads, 512);
+    switch (b) {
+    case 128: flow_batched_kernel<128><<<grid, 256, 0, s>>>(d, count, (int)blocks, (int)pads); break;
+    case 256: flow_batched_kernel<256><<<grid, 256, 0, s>>>(d, count, (int)blocks, (int)pads); break;
+    case 384: flow_batched_kernel<384><<<grid, 256, 0, s>>>(d, count, (int)blocks, (int)pads); break;
+    default: flow_batched_kernel<512><<<grid, 256, 0, s>>>(d, count, (int)blocks, (int)pads); break;
+    }
 }
 
 }  // namespace gl

@@ -3,8 +3,7 @@
 // with blocks of s·b consecutive locations and l(θ) is the sum of the exact
 // log-likelihoods of the blocks.  Nothing outside the blocks is generated or
 // factored: the blocks are independent factorisations of s tile columns each
-// (the last one possibly shorter), advanced together through the fused
-// multi-factorisation launches, one tile step per launch group.
+// (the last one possibly shorter), all in one launch (enqueue_whole).
 //
 // Kriging under the same approximation (the exact-versus-IND prediction
 // comparison of the paper's experiments, with Eq. (5)): applied to the
@@ -64,7 +63,8 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
     const int64_t nblk = (int64_t)start.size();
     const int64_t block = bt * b;  // uniform block length (the likelihood's), for the reported column
     // layout (in doubles): descriptors | total | solve words | per-block results, info |
-    // per block: tiles, x, y, v, logsum, quad, dinv | reordered inputs, keys
+    // per block: tiles, x, y, v, logsum, quad, dinv, progress words | reordered inputs, keys
+    auto word_doubles = [](int64_t n) { return (size_t)flow_words(n, flow_stride(n)) / 2; };
     const size_t desc_d = ((size_t)nblk * sizeof(BatchReq) + 15) / 16 * 2;
     size_t off = desc_d + 8 + BACK_WORDS + 8 * (size_t)nblk + 8 * (size_t)nblk;
     std::vector<size_t> boff(nblk);
@@ -74,7 +74,8 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
         ntb[i] = ceil_div(nb[i], b);
         const int64_t npb = ntb[i] * b;
         boff[i] = off;
-        off += (size_t)tile_count(ntb[i]) * b * b + 3 * npb + 2 * ntb[i] + (ntb[i] & 1) + 64 * npb;
+        off += (size_t)tile_count(ntb[i]) * b * b + 3 * npb + 2 * ntb[i] + 64 * npb + word_doubles(nb[i]);
+        off += off & 1;
     }
     const size_t morton_off = off;
     if (reorder) off += 3 * (size_t)n + (n & 1) + (size_t)npow2_of(n) + 4;
@@ -121,8 +122,11 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
         p += 3 * npb;
         d.logsum = p;
         d.quad = p + ntb[i];
-        p += 2 * ntb[i] + (ntb[i] & 1);
+        p += 2 * ntb[i];
         d.dinv = p;
+        p += 64 * npb;
+        d.words = reinterpret_cast<int32_t *>(p);
+        d.stride = flow_stride(nb[i]);
         d.info = binfo + 8 * i;
         d.res = bres + i;
         d.sx = sx + start[i];
@@ -134,11 +138,10 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
         d.nt = ntb[i];
         d.npad = npb;
     }
-    // The descriptors of every step go to pinned host memory owned by the
-    // context (one region per step), which the asynchronous copies read until
-    // the stream passes them; the previous call's copies are waited for
-    // before the memory is rewritten or replaced.
-    const size_t entries = (size_t)bt * (size_t)nblk;
+    // The descriptors go to pinned host memory owned by the context, which the
+    // asynchronous copy reads until the stream passes it; the previous call's
+    // copy is waited for before the memory is rewritten or replaced.
+    const size_t entries = (size_t)nblk;
     if (ctx->ind_done) GL_HIP_TRY(hipEventSynchronize(ctx->ind_done));
     else GL_HIP_TRY(hipEventCreateWithFlags(&ctx->ind_done, hipEventDisableTiming));
     if (entries > ctx->ind_host_cap) {
@@ -149,23 +152,9 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
                                  hipHostMallocDefault));
         ctx->ind_host_cap = entries;
     }
-    BatchReq *h = ctx->ind_host;
-    for (int64_t k = 0; k < bt; ++k) {
-        int cnt = 0;
-        for (int64_t i = 0; i < nblk; ++i) {
-            if (k >= ntb[i]) continue;  // the last block may have fewer tile columns
-            BatchReq &d = h[cnt++];
-            d = proto[i];
-            d.dinv = proto[i].dinv + k * 64 * (int64_t)b;
-            d.k = k;
-            d.is_new = k == 0;
-            d.finishing = k == ntb[i] - 1;
-        }
-        if (cnt == 0) break;
-        const int rc = enqueue_step(h, ddesc, cnt, b, s, nullptr);
-        if (rc != GL_OK) return rc;
-        h += cnt;
-    }
+    std::copy(proto.begin(), proto.end(), ctx->ind_host);
+    const int rc = enqueue_whole(ctx->ind_host, ddesc, (int)nblk, b, s, nullptr);
+    if (rc != GL_OK) return rc;
     GL_HIP_TRY(hipEventRecord(ctx->ind_done, s));
     ind_total_kernel<<<1, 64, 0, s>>>(bres, nblk, block, total);
     GL_HIP_TRY(hipGetLastError());

@@ -23,7 +23,6 @@
 // CU has room for its registers and LDS: its footprint is kept at what the
 // general path needs (a fully unrolled block read raised the registers and
 // made some calls wait out a whole trailing launch).
-#include "batch.hpp"
 #include "common.hpp"
 #include "mfma.hpp"
 #include "potrf64.hpp"
@@ -274,23 +273,15 @@ __device__ __forceinline__ void potrf_general(double *__restrict__ tiles, int64_
 }
 
 template <int B>
-__device__ __forceinline__ void potrf_body(double *__restrict__ tiles, int64_t k, int64_t n,
-                                           int64_t *__restrict__ info, double *__restrict__ logsum,
-                                           double *__restrict__ dinv)
+__global__ __launch_bounds__(256, 2) void potrf_kernel(double *__restrict__ tiles, int64_t k, int64_t n,
+                                                       int64_t *__restrict__ info,
+                                                       double *__restrict__ logsum,
+                                                       double *__restrict__ dinv)
 {
     if (*info != 0) return;
     __builtin_amdgcn_s_setprio(3);  // critical path of the step schedule
     if constexpr (B == 128) potrf_tile128(tiles, k, n, info, logsum, dinv);
     else potrf_general<B>(tiles, k, n, info, logsum, dinv);
-}
-
-template <int B>
-__global__ __launch_bounds__(256, 2) void potrf_kernel(double *__restrict__ tiles, int64_t k, int64_t n,
-                                                    int64_t *__restrict__ info,
-                                                    double *__restrict__ logsum,
-                                                    double *__restrict__ dinv)
-{
-    potrf_body<B>(tiles, k, n, info, logsum, dinv);
 }
 
 void launch_potrf(double *tiles, int b, int64_t k, int64_t n, int64_t *info, double *logsum,
@@ -301,23 +292,6 @@ void launch_potrf(double *tiles, int b, int64_t k, int64_t n, int64_t *info, dou
     case 256: potrf_kernel<256><<<1, 256, 0, s>>>(tiles, k, n, info, logsum, dinv); break;
     case 384: potrf_kernel<384><<<1, 256, 0, s>>>(tiles, k, n, info, logsum, dinv); break;
     default: potrf_kernel<512><<<1, 256, 0, s>>>(tiles, k, n, info, logsum, dinv); break;
-    }
-}
-
-template <int B>
-__global__ __launch_bounds__(256, 2) void potrf_batched_kernel(const BatchReq *__restrict__ d)
-{
-    const BatchReq &r = d[blockIdx.x];
-    potrf_body<B>(r.tiles, r.k, r.n, r.info, r.logsum, r.dinv);
-}
-
-void launch_potrf_batched(int b, const BatchReq *d, int count, hipStream_t s)
-{
-    switch (b) {
-    case 128: potrf_batched_kernel<128><<<count, 256, 0, s>>>(d); break;
-    case 256: potrf_batched_kernel<256><<<count, 256, 0, s>>>(d); break;
-    case 384: potrf_batched_kernel<384><<<count, 256, 0, s>>>(d); break;
-    default: potrf_batched_kernel<512><<<count, 256, 0, s>>>(d); break;
     }
 }
 

@@ -3,17 +3,16 @@
 //
 // A scheduler thread serves requests in two ways.
 //
-// Continuous batching (FP64 requests with n <= small_n): admitted requests
-// join a resident set; every scheduler tick advances each resident request by
-// one step of its tiled factorisation through one fused launch per kernel
-// (staging and Σ generation for newcomers, POTRF, forward diagonal solve,
-// TRSM, forward update, trailing update, final reduction for those whose last
-// step it is).  A launch covers all residents of a cohort, each at its own
-// step, so requests that arrive while others are on the device join at the
-// next tick and leave when done.  Residents are spread over two cohorts with
-// their own streams; each cohort may have two ticks in flight.  Each request runs the
-// same per-request code as a single evaluation with tile 256, so its result
-// does not depend on the batch it rides in.
+// Batching (FP64 requests with n <= small_n): admitted requests join a
+// resident set; a scheduler tick enqueues the whole evaluations of a cohort's
+// residents in fused launches (staging, Σ generation, all factorisations and
+// forward solves in one launch, final reductions; see enqueue_whole).
+// Requests that arrive meanwhile join the next tick.  Residents are spread
+// over two cohorts with their own streams, so one cohort's tail (few blocks
+// left, bound by its chain) runs beside the other's bulk; each cohort may have
+// two ticks in flight.  Each request runs the same per-request code as a single
+// evaluation with tile 256, so its result does not depend on the batch it
+// rides in.
 //
 // Other requests use device slots (a stream, a lookahead lane, a workspace
 // and a pinned result buffer each) and run their whole evaluation on the
@@ -126,8 +125,6 @@ constexpr int TICK_MAX = 64;    // residents per tick
 struct Resident {
     Request *req = nullptr;
     Work *w = nullptr;
-    int64_t k = 0;
-    bool is_new = true;
 };
 
 struct TickBuf {
@@ -277,7 +274,7 @@ bool make_room(lq_queue *q, size_t need, size_t mine, const Slot *keep_slot)
     return held_bytes(q) - mine + need <= q->budget;
 }
 
-// Enqueue one tick of cohort c: every resident advances by one step.
+// Enqueue one tick of cohort c: the whole evaluations of its residents.
 int build_tick(lq_queue *q, Cohort &co)
 {
     TickBuf &tb = co.ring[co.ring_next];
@@ -291,7 +288,7 @@ int build_tick(lq_queue *q, Cohort &co)
         d.x = w.x;
         d.y = w.y;
         d.v = w.v;
-        d.dinv = w.dinv_k(r.k);
+        d.dinv = w.dinv;
         d.logsum = w.logsum;
         d.quad = w.quad;
         d.info = w.info;
@@ -305,33 +302,24 @@ int build_tick(lq_queue *q, Cohort &co)
         d.n = w.n;
         d.nt = w.nt;
         d.npad = w.npad;
-        d.k = r.k;
-        d.is_new = r.is_new ? 1 : 0;
-        d.finishing = (r.k == w.nt - 1) ? 1 : 0;
+        d.k = 0;
+        d.words = reinterpret_cast<int32_t *>(w.keys);  // the tick's requests are not reordered
+        d.stride = flow_stride(n);
     }
     hipStream_t s = co.s;
     int launches = 0;
     const auto h0 = std::chrono::steady_clock::now();
     GL_HIP_TRY(hipEventRecord(tb.start, s));
-    const int rc = enqueue_step(tb.host, tb.dev, count, TICK_B, s, &launches);
+    const int rc = enqueue_whole(tb.host, tb.dev, count, TICK_B, s, &launches);
     if (rc != GL_OK) return rc;
     tb.finishing.clear();
     GL_HIP_TRY(hipGetLastError());
-    std::vector<Resident> keep;
-    keep.reserve(co.residents.size());
-    for (int i = 0; i < count; ++i) {
-        Resident r = co.residents[i];
-        r.is_new = false;
-        if (tb.host[i].finishing) {
-            GL_HIP_TRY(hipMemcpyAsync(&tb.res_h[tb.finishing.size()], r.w->res, sizeof(DevResult),
-                                      hipMemcpyDeviceToHost, s));
-            tb.finishing.push_back(r);
-        } else {
-            r.k += 1;
-            keep.push_back(r);
-        }
+    for (const Resident &r : co.residents) {
+        GL_HIP_TRY(hipMemcpyAsync(&tb.res_h[tb.finishing.size()], r.w->res, sizeof(DevResult), hipMemcpyDeviceToHost,
+                                  s));
+        tb.finishing.push_back(r);
     }
-    co.residents.swap(keep);
+    co.residents.clear();
     GL_HIP_TRY(hipEventRecord(tb.done, s));
     tb.busy = true;
     co.ticks.push_back(co.ring_next);

@@ -22,10 +22,10 @@ namespace gl {
 // is split over four thread groups with fixed-order partial sums.  The tile's
 // part of wᵀw (rows < n) goes to quad_part[k], summed by 128-row blocks.
 template <int B>
-__device__ __forceinline__ void fwd_diag_body(const double *__restrict__ tiles, int64_t k, int64_t n,
-                                              double *__restrict__ v, double *__restrict__ quad_part,
-                                              const double *__restrict__ dinv,
-                                              const int64_t *__restrict__ info)
+__global__ __launch_bounds__(256) void fwd_diag_kernel(const double *__restrict__ tiles, int64_t k, int64_t n,
+                                                       double *__restrict__ v, double *__restrict__ quad_part,
+                                                       const double *__restrict__ dinv,
+                                                       const int64_t *__restrict__ info)
 {
     if (info && *info != 0) return;
     __builtin_amdgcn_s_setprio(3);  // critical path of the step schedule
@@ -87,27 +87,16 @@ __device__ __forceinline__ void fwd_diag_body(const double *__restrict__ tiles, 
     }
 }
 
-template <int B>
-__global__ __launch_bounds__(256) void fwd_diag_kernel(const double *__restrict__ tiles, int64_t k,
-                                                       int64_t n, double *__restrict__ v,
-                                                       double *__restrict__ quad_part,
-                                                       const double *__restrict__ dinv,
-                                                       const int64_t *__restrict__ info)
-{
-    fwd_diag_body<B>(tiles, k, n, v, quad_part, dinv, info);
-}
-
 // v_i -= L_ik v_k for every tile i > k, one 128-column block of L_ik after the
-// other; workgroup (tile i = k + 1 + tix, 64-row strip).
+// other; workgroup (tile i = k + 1 + x, 64-row strip y).
 template <int B>
-__device__ __forceinline__ void fwd_update_body(const double *__restrict__ tiles, int64_t k,
-                                                double *__restrict__ v, const int64_t *__restrict__ info,
-                                                int64_t tix, int strip)
+__global__ __launch_bounds__(256) void fwd_update_kernel(const double *__restrict__ tiles, int64_t k,
+                                                         double *__restrict__ v, const int64_t *__restrict__ info)
 {
     if (info && *info != 0) return;
     __builtin_amdgcn_s_setprio(3);
-    const int64_t i = k + 1 + tix;
-    const int r0 = strip * 64;
+    const int64_t i = k + 1 + blockIdx.x;
+    const int r0 = blockIdx.y * 64;
     const double *L = tiles + tile_offset(i, k, B);
     const int tid = threadIdx.x;
     __shared__ double wk[B];
@@ -129,14 +118,6 @@ __device__ __forceinline__ void fwd_update_body(const double *__restrict__ tiles
         for (int s = 0; s < B / 128; ++s) x -= (red[s][0][r] + red[s][1][r]) + (red[s][2][r] + red[s][3][r]);
         v[i * B + r0 + r] = x;
     }
-}
-
-template <int B>
-__global__ __launch_bounds__(256) void fwd_update_kernel(const double *__restrict__ tiles, int64_t k,
-                                                         double *__restrict__ v,
-                                                         const int64_t *__restrict__ info)
-{
-    fwd_update_body<B>(tiles, k, v, info, blockIdx.x, blockIdx.y);
 }
 
 // z_i = Σ_{j<i} L_ij e_j + tril(L_ii) e_i; workgroup (i, 64-row strip).
@@ -227,23 +208,6 @@ __global__ void tiles_to_dense_kernel(const double *__restrict__ tiles, int b, i
     }
 }
 
-template <int B>
-__global__ __launch_bounds__(256) void fwd_diag_batched_kernel(const BatchReq *__restrict__ d)
-{
-    const BatchReq &r = d[blockIdx.x];
-    fwd_diag_body<B>(r.tiles, r.k, r.n, r.v, r.quad, r.dinv, r.info);
-}
-
-template <int B>
-__global__ __launch_bounds__(256) void fwd_update_batched_kernel(const BatchReq *__restrict__ d, int count)
-{
-    const int64_t g = blockIdx.x;
-    const int r = GL_BATCH_FIND(d, count, g, o_trsm);
-    const BatchReq &q = d[r];
-    const int64_t local = g - q.o_trsm;
-    fwd_update_body<B>(q.tiles, q.k, q.v, q.info, local / (B / 64), (int)(local % (B / 64)));
-}
-
 __global__ void final_batched_kernel(const BatchReq *__restrict__ d)
 {
     const BatchReq &r = d[blockIdx.x];
@@ -251,7 +215,7 @@ __global__ void final_batched_kernel(const BatchReq *__restrict__ d)
     final_reduce_body(r.logsum, r.quad, r.nt, r.n, r.info, r.res);
 }
 
-// Padded copies of new requests' inputs, and their info word cleared.
+// Padded copies of the requests' inputs, and their info and progress words cleared.
 __global__ void stage_batched_kernel(const BatchReq *__restrict__ d, int count)
 {
     const int64_t g = blockIdx.x;
@@ -259,32 +223,12 @@ __global__ void stage_batched_kernel(const BatchReq *__restrict__ d, int count)
     const BatchReq &q = d[r];
     const int64_t i = (g - q.o_stage) * 256 + threadIdx.x;
     if (i == 0) *q.info = 0;
+    if (i < flow_words(q.n, q.stride)) q.words[i] = 0;  // fewer than npad
     if (i >= q.npad) return;
     const bool in = i < q.n;
     q.x[i] = in ? q.sx[i] : 0.0;
     q.y[i] = in ? q.sy[i] : 0.0;
     q.v[i] = in ? q.sz[i] : 0.0;
-}
-
-void launch_fwd_diag_batched(int b, const BatchReq *d, int count, hipStream_t s)
-{
-    switch (b) {
-    case 128: fwd_diag_batched_kernel<128><<<count, 256, 0, s>>>(d); break;
-    case 256: fwd_diag_batched_kernel<256><<<count, 256, 0, s>>>(d); break;
-    case 384: fwd_diag_batched_kernel<384><<<count, 256, 0, s>>>(d); break;
-    default: fwd_diag_batched_kernel<512><<<count, 256, 0, s>>>(d); break;
-    }
-}
-
-void launch_fwd_update_batched(int b, const BatchReq *d, int count, int64_t blocks, hipStream_t s)
-{
-    if (blocks <= 0) return;
-    switch (b) {
-    case 128: fwd_update_batched_kernel<128><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    case 256: fwd_update_batched_kernel<256><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    case 384: fwd_update_batched_kernel<384><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    default: fwd_update_batched_kernel<512><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    }
 }
 
 void launch_final_batched(const BatchReq *d, int count, hipStream_t s)

@@ -16,7 +16,6 @@
 // index is remapped so that each XCD works on a contiguous run of blocks,
 // i.e. on whole tiles and on neighbouring tiles of one column, which share
 // the L_jk operand in that XCD's L2.
-#include "batch.hpp"
 #include "common.hpp"
 #include "mfma.hpp"
 
@@ -237,43 +236,6 @@ void launch_trailing(double *tiles, int b, int64_t nt, int64_t k, int64_t jbeg, 
         launch_trailing_t<true>(tiles, b, nt, k, jbeg, jend, info, critical, s);
     else
         launch_trailing_t<false>(tiles, b, nt, k, jbeg, jend, info, critical, s);
-}
-
-// Fused trailing updates of many requests, each at its own step k (columns
-// k+1 .. nt-1).  The flattened block index is remapped XCD-contiguously.
-template <int B>
-__global__ __launch_bounds__(256, 2) void trailing_batched_kernel(const BatchReq *__restrict__ d, int count,
-                                                                  int64_t nblocks)
-{
-    constexpr int SB = B / GB;
-    constexpr int SUB = SB * SB;
-    const int64_t G = gridDim.x;
-    const int64_t g = blockIdx.x;
-    const int64_t lid = (g & 7) * (G >> 3) + (g >> 3);
-    if (lid >= nblocks) return;
-    const int r = GL_BATCH_FIND(d, count, lid, o_tr);
-    const BatchReq &q = d[r];
-    if (*q.info != 0) return;
-    const int64_t local = lid - q.o_tr;
-    const int64_t t = local / SUB;
-    const int sub = (int)(local % SUB);
-    int64_t i, j;
-    trailing_tile(t, q.k + 1, q.nt, i, j);
-    const int rb = sub / SB, cb = sub % SB;
-    if (i == j && cb > rb) return;
-    trailing_block_body<B>(q.tiles, q.k, i, j, rb, cb);
-}
-
-void launch_trailing_batched(int b, const BatchReq *d, int count, int64_t blocks, hipStream_t s)
-{
-    if (blocks <= 0) return;
-    const int64_t grid = ceil_div(blocks, 8) * 8;
-    switch (b) {
-    case 128: trailing_batched_kernel<128><<<(unsigned)grid, 256, 0, s>>>(d, count, blocks); break;
-    case 256: trailing_batched_kernel<256><<<(unsigned)grid, 256, 0, s>>>(d, count, blocks); break;
-    case 384: trailing_batched_kernel<384><<<(unsigned)grid, 256, 0, s>>>(d, count, blocks); break;
-    default: trailing_batched_kernel<512><<<(unsigned)grid, 256, 0, s>>>(d, count, blocks); break;
-    }
 }
 
 // Trailing updates of the tiles listed in `list` (count tiles, (i, j) pairs);

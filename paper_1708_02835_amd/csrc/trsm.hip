@@ -10,7 +10,6 @@
 // `dinv` by the POTRF of the same step.  The product streams 16-column chunks
 // of X and L_kk through LDS, double-buffered; X[:, 0:J] was written by this
 // workgroup in earlier blocks (visible after the block barrier).
-#include "batch.hpp"
 #include "common.hpp"
 #include "mfma.hpp"
 
@@ -128,23 +127,15 @@ __device__ __forceinline__ void trsm_core(const double *__restrict__ L, double *
     }
 }
 
-// Strip `strip` of panel tile i = k + 1 + tix.
-template <int B>
-__device__ __forceinline__ void trsm_body(double *__restrict__ tiles, int64_t k,
-                                          const double *__restrict__ dinv,
-                                          const int64_t *__restrict__ info, int64_t tix, int strip)
-{
-    if (*info != 0) return;
-    __builtin_amdgcn_s_setprio(3);  // critical path of the step schedule
-    trsm_core<B>(tiles + tile_offset(k, k, B), tiles + tile_offset(k + 1 + tix, k, B), dinv, strip);
-}
-
+// Workgroup (tile i = k + 1 + x, strip y).
 template <int B>
 __global__ __launch_bounds__(256) void trsm_kernel(double *__restrict__ tiles, int64_t k,
                                                    const double *__restrict__ dinv,
                                                    const int64_t *__restrict__ info)
 {
-    trsm_body<B>(tiles, k, dinv, info, blockIdx.x, blockIdx.y);
+    if (*info != 0) return;
+    __builtin_amdgcn_s_setprio(3);  // critical path of the step schedule
+    trsm_core<B>(tiles + tile_offset(k, k, B), tiles + tile_offset(k + 1 + blockIdx.x, k, B), dinv, blockIdx.y);
 }
 
 void launch_trsm(double *tiles, int b, int64_t nt, int64_t k, const double *dinv, const int64_t *info,
@@ -158,27 +149,6 @@ void launch_trsm(double *tiles, int b, int64_t nt, int64_t k, const double *dinv
     case 256: trsm_kernel<256><<<grid, 256, 0, s>>>(tiles, k, dinv, info); break;
     case 384: trsm_kernel<384><<<grid, 256, 0, s>>>(tiles, k, dinv, info); break;
     default: trsm_kernel<512><<<grid, 256, 0, s>>>(tiles, k, dinv, info); break;
-    }
-}
-
-template <int B>
-__global__ __launch_bounds__(256) void trsm_batched_kernel(const BatchReq *__restrict__ d, int count)
-{
-    const int64_t g = blockIdx.x;
-    const int r = GL_BATCH_FIND(d, count, g, o_trsm);
-    const BatchReq &q = d[r];
-    const int64_t local = g - q.o_trsm;
-    trsm_body<B>(q.tiles, q.k, q.dinv, q.info, local / (B / TB), (int)(local % (B / TB)));
-}
-
-void launch_trsm_batched(int b, const BatchReq *d, int count, int64_t blocks, hipStream_t s)
-{
-    if (blocks <= 0) return;
-    switch (b) {
-    case 128: trsm_batched_kernel<128><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    case 256: trsm_batched_kernel<256><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    case 384: trsm_batched_kernel<384><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
-    default: trsm_batched_kernel<512><<<(unsigned)blocks, 256, 0, s>>>(d, count); break;
     }
 }
 
