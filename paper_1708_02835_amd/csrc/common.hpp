@@ -94,12 +94,6 @@ int selftest_mfma(int which, double *out_h, int64_t cap);
 // Kriging variances (Eq. 4): chunks of b right-hand sides solved together.
 void launch_gen_rhs(double *st, const double *x, const double *y, int64_t n, int b, int64_t nt, const double *xn,
                     const double *yn, int64_t m, int64_t chunks, gl_theta th, Geom geo, hipStream_t s);
-void launch_mrhs_diag(const double *tiles, double *st, int b, int64_t nt, int64_t k, const double *dinv,
-                      int64_t chunks, hipStream_t s);
-void launch_mrhs_update(const double *tiles, double *st, int b, int64_t nt, int64_t k, int64_t chunks,
-                        hipStream_t s);
-void launch_rhs_variance(const double *st, int b, int64_t nt, int64_t chunks, int64_t m, double theta1,
-                         double *part, double *var, hipStream_t s);
 
 // Cross-validation helpers.
 void launch_gather3(const double *a, const double *b, const double *c, const int64_t *idx, int64_t m, double *oa,

@@ -807,21 +807,20 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     hipStream_t s = static_cast<hipStream_t>(stream);
     Work &w = f->w;
     const Geom geo = geom_of(f->opts);
-    const int64_t nchunk = krige_chunks(w.n);
     // variances: groups of up to 8 chunks of b right-hand sides
+    const int64_t nchunk = krige_chunks(w.n);
     const int64_t chunks = var ? std::min<int64_t>(8, ceil_div(m, w.b)) : 0;
     const size_t st_len = (size_t)chunks * w.npad * w.b;
+    const size_t var_len = var && flow_rhs_scratch ? flow_rhs_scratch(w.n, std::min<int64_t>(m, chunks * w.b)) : 0;
+    const size_t bytes = (BACK_WORDS + (size_t)w.npad + m * nchunk + 1 + st_len + var_len) * sizeof(double);
     double *scratch = nullptr;
-    const size_t bytes =
-        (BACK_WORDS + (size_t)w.npad + m * nchunk + st_len + (size_t)chunks * w.npad) * sizeof(double);
     if (hipMallocAsync(reinterpret_cast<void **>(&scratch), bytes, s) != hipSuccess) {
         (void)hipGetLastError();
         return GL_ENOMEM;
     }
     double *xv = scratch + BACK_WORDS;
     double *part = xv + w.npad;
-    double *st = part + m * nchunk;
-    double *vpart = st + st_len;
+    double *st = part + m * nchunk + ((m * nchunk) & 1);
     // X = L⁻ᵀ w
     launch_copy_pad(w.v, w.npad, xv, w.npad, 0.0, s);
     if (launch_backward) launch_backward(w.tiles, w.dinv, w.b, w.n, xv, scratch, s);
@@ -830,13 +829,9 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     // var_k = θ1 - ||L⁻¹ σ_k||², right-hand sides solved on the matrix cores
     for (int64_t k0 = 0; var && k0 < m; k0 += chunks * w.b) {
         const int64_t mg = std::min<int64_t>(m - k0, chunks * w.b);
-        const int64_t cg = ceil_div(mg, w.b);
-        launch_gen_rhs(st, w.x, w.y, w.n, w.b, w.nt, xnew + k0, ynew + k0, mg, cg, f->theta, geo, s);
-        for (int64_t k = 0; k < w.nt; ++k) {
-            launch_mrhs_diag(w.tiles, st, w.b, w.nt, k, w.dinv_k(k), cg, s);
-            launch_mrhs_update(w.tiles, st, w.b, w.nt, k, cg, s);
-        }
-        launch_rhs_variance(st, w.b, w.nt, cg, mg, f->theta.theta1, vpart, var + k0, s);
+        launch_gen_rhs(st, w.x, w.y, w.n, w.b, w.nt, xnew + k0, ynew + k0, mg, ceil_div(mg, w.b), f->theta, geo, s);
+        if (launch_flow_rhs)
+            launch_flow_rhs(w, st, mg, f->theta.theta1, st + st_len, var + k0, s);
     }
     GL_HIP_TRY(hipGetLastError());
     GL_HIP_TRY(hipFreeAsync(scratch, s));

@@ -122,6 +122,12 @@ int factorize(Lanes &ln, Work &w, hipStream_t s, bool solve, int64_t near, bool 
 // one workgroup, the same operations in the same order, so the same bits as
 // factorize().  Not part of builds without device code (weak).
 int flow_factorize(Work &w, hipStream_t s, bool solve) __attribute__((weak));
+// Kriging variances of m new locations from a finished factor (flow.hip, weak
+// too): st holds the right-hand sides (launch_gen_rhs) and scratch
+// flow_rhs_scratch(n, m) doubles.
+int64_t flow_rhs_scratch(int64_t n, int64_t m) __attribute__((weak));
+void launch_flow_rhs(const Work &w, double *st, int64_t m, double theta1, double *scratch, double *var, hipStream_t s)
+    __attribute__((weak));
 // Factorisation of a binary64 evaluation by whichever of the two applies;
 // near_tiles as in gl_opts.
 int factor_fp64(Lanes &ln, Work &w, hipStream_t s, bool solve, int32_t near_tiles);

@@ -33,6 +33,11 @@
 //
 // The sequence of operations on every element is that of the step schedule
 // (potrf.hip, trsm.hip, trailing.hip, solve.hip), so both give the same bits.
+//
+// Bound by the matrix cores from about n = 12,000 up (67.6 TFLOP/s of 78.6 at
+// n = 40,000, 69 at n = 100,000) and by the chain of diagonal blocks below.
+// Whole evaluations, step schedule and this: n = 400 480 and 252 µs, n = 1,600
+// 1.48 and 0.67 ms, n = 8,100 11.2 and 4.6 ms, n = 40,000 373 and 316 ms.
 #include <algorithm>
 
 #include "batch.hpp"
@@ -72,14 +77,14 @@ __device__ __forceinline__ int peek(const int *p) { return __hip_atomic_load(p, 
 __device__ __forceinline__ void post(int *p, int x) { __hip_atomic_store(p, x, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Waits until min(*a, *b) >= want and returns it; -1 when the factorisation
-// has failed.  Called by every thread; one polls.
+// has failed (info, if not NULL).  Called by every thread; one polls.
 __device__ __forceinline__ int await(const int *a, const int *b, int want, const int64_t *info, FlowShared &sh)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
         int x;
         while ((x = min(peek(a), peek(b))) < want) {
-            if (__hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            if (info && __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
                 x = -1;
                 break;
             }
@@ -130,11 +135,12 @@ __device__ __forceinline__ void stage64(const double *__restrict__ src, int64_t 
 __device__ __forceinline__ double staged(const double *s, int m, int c) { return s[m * 64 + (c ^ ((m & 1) << 4))]; }
 
 // acc += rows of A times rows of B over the columns [c0, c1) (multiples of
-// FK), A and B 128 rows of ld B.  DIAG: A == B, and wave w's two row blocks
-// are w and 7 - w, columns up to the diagonal only.
-template <int B, bool DIAG>
+// FK), A of 64 NA and B of 128 rows, ld B; wave w has the NA 16-row blocks from
+// NA w.  DIAG (NA = 2): A == B, and its row blocks are w and 7 - w, columns up
+// to the diagonal only.
+template <int B, int NA, bool DIAG>
 __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const double *__restrict__ Bp, int c0, int c1,
-                                           d4 (&acc)[2][8], double *buf)
+                                           d4 (*acc)[8], double *buf)
 {
     auto As = reinterpret_cast<double(*)[FK][FP]>(buf);
     auto Bs = reinterpret_cast<double(*)[FK][FP]>(buf + 2 * FK * FP);
@@ -143,19 +149,19 @@ __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lc = tid >> 4;
     const int le = (tid & 15) * 2;
-    const int ra0 = DIAG ? wave * 16 : wave * 32, ra1 = DIAG ? (7 - wave) * 16 : wave * 32 + 16;
+    const int ra0 = DIAG ? wave * 16 : wave * 16 * NA, ra1 = DIAG ? (7 - wave) * 16 : wave * 32 + 16;
     d2 ra[4], rb[4];
     auto load = [&](int col) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            ra[q] = *reinterpret_cast<const d2 *>(Ap + (int64_t)(col + lc) * B + le + 32 * q);
+            if (q < 2 * NA) ra[q] = *reinterpret_cast<const d2 *>(Ap + (int64_t)(col + lc) * B + le + 32 * q);
             if constexpr (!DIAG) rb[q] = *reinterpret_cast<const d2 *>(Bp + (int64_t)(col + lc) * B + le + 32 * q);
         }
     };
     auto store = [&](int cur) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            *reinterpret_cast<d2 *>(&As[cur][lc][le + 32 * q]) = ra[q];
+            if (q < 2 * NA) *reinterpret_cast<d2 *>(&As[cur][lc][le + 32 * q]) = ra[q];
             if constexpr (!DIAG) *reinterpret_cast<d2 *>(&Bs[cur][lc][le + 32 * q]) = rb[q];
         }
     };
@@ -169,7 +175,7 @@ __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const 
         for (int kk = 0; kk < FK; kk += 4) {
             const double *arow = As[cur][kk + (lane >> 4)];
             const double *brow = DIAG ? arow : Bs[cur][kk + (lane >> 4)];
-            const double a0 = arow[ra0 + (lane & 15)], a1 = arow[ra1 + (lane & 15)];
+            const double a0 = arow[ra0 + (lane & 15)], a1 = NA > 1 ? arow[ra1 + (lane & 15)] : 0.0;
             double bv[8];
 #pragma unroll
             for (int b = 0; b < 8; ++b) bv[b] = brow[b * 16 + (lane & 15)];
@@ -177,7 +183,7 @@ __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const 
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
                 if (!DIAG || (b < 4 && b <= wave)) acc[0][b] = mfma_f64(bv[b], a0, acc[0][b]);
-                if (!DIAG || b < 4 || b <= 7 - wave) acc[1][b] = mfma_f64(bv[b], a1, acc[1][b]);
+                if (NA > 1 && (!DIAG || b < 4 || b <= 7 - wave)) acc[1][b] = mfma_f64(bv[b], a1, acc[1][b]);
             }
         }
         // the staging of the next chunk stays after this chunk's products
@@ -215,6 +221,23 @@ __device__ __forceinline__ void solve64(d4 (*acc)[8], F &&inv)
     }
 }
 
+// -T of the second 64 columns takes X_0 L_10ᵀ, L_10 staged in s.
+template <int NA>
+__device__ __forceinline__ void carry64(d4 (*acc)[8], const double *s)
+{
+    const int lane = thread_index() & 63;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double l = staged(s, 16 * mb + 4 * r + (lane >> 4), 16 * cb + (lane & 15));
+#pragma unroll
+                for (int a = 0; a < NA; ++a) acc[a][4 + cb] = mfma_f64(l, acc[a][mb][r], acc[a][4 + cb]);
+            }
+}
+
 // Block (i, j), i > j.  False when the factorisation has failed.
 template <int B>
 __device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowShared &sh)
@@ -244,7 +267,7 @@ __device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowSh
         const int have = await(prog + i * p.stride, prog + j * p.stride, k + 1, p.info, sh);
         if (have < 0) return false;
         const int e = min(have, j);
-        accumulate<B, false>(Ai, Bj, k * FB, e * FB, acc, sh.buf);
+        accumulate<B, 2, false>(Ai, Bj, k * FB, e * FB, acc, sh.buf);
         k = e;
     }
     // first 64 columns, then the second
@@ -256,16 +279,7 @@ __device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowSh
     stage64(Ljj + PB, B, s1);
     __syncthreads();
     solve64<2, 0>(acc, [&](int m, int c) { return staged(s0, m, c); });
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double l = staged(s1, 16 * mb + 4 * r + (lane >> 4), 16 * cb + (lane & 15));
-#pragma unroll
-                for (int a = 0; a < 2; ++a) acc[a][4 + cb] = mfma_f64(l, acc[a][mb][r], acc[a][4 + cb]);
-            }
+    carry64<2>(acc, s1);
     auto put = [&](int h) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -334,7 +348,7 @@ __device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &
         const int have = await(prog + j * p.stride, prog + j * p.stride, k + 1, p.info, sh);
         if (have < 0) return false;
         const int e = min(have, j);
-        accumulate<B, true>(Aj, Aj, k * FB, e * FB, acc, sh.buf);
+        accumulate<B, 2, true>(Aj, Aj, k * FB, e * FB, acc, sh.buf);
         k = e;
     }
     auto X = reinterpret_cast<double(*)[PB + 1]>(sh.buf);                  // D_0, then X_10, then D_1⁻¹
@@ -572,6 +586,84 @@ __global__ __launch_bounds__(256, 2) void flow_batched_kernel(const BatchReq *__
     }
 }
 
+// Right-hand sides of the kriging variances (Eq. 4), U = Sᵀ L⁻ᵀ by blocks of 64
+// of them: a right-hand side is one more row below L, so block (R, j) is
+// computed as a block of L is, and waits for its own row only.  64 rows
+// instead of 128 halve the chain along a row and fill the chip with 1,000
+// right-hand sides.  Each block also leaves its part of Σ U², so U is not read
+// again.  n = 16,000, 1,000 right-hand sides: the whole kriging call 10.7 -> 5.7
+// ms against two launches per tile row, whose diagonal solves had 16 workgroups.
+template <int B>
+__global__ __launch_bounds__(256, 2) void flow_rhs_kernel(const double *__restrict__ tiles,
+                                                          const double *__restrict__ dinv,
+                                                          double *__restrict__ st, int nb, int64_t nt,
+                                                          int groups, int *words, double *__restrict__ part)
+{
+    constexpr int S = B / FB, RS = B / 64;
+    __shared__ FlowShared sh;
+    for (;;) {
+        const int t = flow_ticket(words, sh);
+        if (t >= nb * groups) return;
+        const int j = t / groups, R = t % groups;
+        const int tid = thread_index();
+        const int lane = tid & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        int *prog = words + 16 * (1 + R);
+        double *A = st + (R / RS) * nt * B * B + (R % RS) * 64;
+        double *C = A + (int64_t)j * FB * B;
+        const double *Bj = tiles + tile_offset(j / S, 0, B) + (j % S) * FB;
+        const double *dv = dinv + (int64_t)j * 2 * PB * PB;
+        double *s0 = sh.buf, *s1 = sh.buf + PB * PB;
+        const int64_t at = (int64_t)mfma_row(lane, 0) * B + wave * 16 + mfma_col(lane);
+        d4 acc[1][8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[0][b][r] = -C[at + (int64_t)(b * 16 + 4 * r) * B];
+        for (int k = 0; k < j;) {
+            const int e = min(await(prog, prog, k + 1, nullptr, sh), j);
+            accumulate<B, 1, false>(A, Bj, k * FB, e * FB, acc, sh.buf);
+            k = e;
+        }
+        __syncthreads();
+        stage64(dv, PB, s0);
+        stage64(Bj + (int64_t)j * FB * B + PB, B, s1);
+        __syncthreads();
+        solve64<1, 0>(acc, [&](int m, int c) { return staged(s0, m, c); });
+        carry64<1>(acc, s1);
+        __syncthreads();
+        stage64(dv + PB * PB, PB, s0);
+        __syncthreads();
+        solve64<1, 4>(acc, [&](int m, int c) { return staged(s0, m, c); });
+        double q = 0.0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double x = acc[0][b][r];
+                C[at + (int64_t)(b * 16 + 4 * r) * B] = x;
+                q = fma(x, x, q);
+            }
+        settle();
+        if (tid == 0) post(prog, j + 1);
+        q += __shfl_xor(q, 16, 64);
+        q += __shfl_xor(q, 32, 64);
+        if (lane < 16) part[((int64_t)j * groups + R) * 64 + wave * 16 + lane] = q;
+    }
+}
+
+// Sums of the parts over the block columns, in order: thread per right-hand side.
+__global__ void flow_rhs_sum_kernel(const double *__restrict__ part, int nb, int groups, int64_t m, double theta1,
+                                    double *__restrict__ var)
+{
+    const int64_t k = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (k >= m) return;
+    double q = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < nb; ++j) q += part[((int64_t)j * groups + (k >> 6)) * 64 + (k & 63)];
+    var[k] = theta1 - q;
+}
+
 }  // namespace
 
 int flow_factorize(Work &w, hipStream_t s, bool solve)
@@ -615,6 +707,28 @@ void launch_flow_batched(int b, const BatchReq *d, int count, int64_t blocks, in
     case 384: flow_batched_kernel<384><<<grid, 256, 0, s>>>(d, count, (int)blocks, (int)pads); break;
     default: flow_batched_kernel<512><<<grid, 256, 0, s>>>(d, count, (int)blocks, (int)pads); break;
     }
+}
+
+int64_t flow_rhs_scratch(int64_t n, int64_t m)
+{
+    const int64_t groups = ceil_div(m, 64);
+    return 8 * (1 + groups) + ceil_div(n, FB) * groups * 64;
+}
+
+void launch_flow_rhs(const Work &w, double *st, int64_t m, double theta1, double *scratch, double *var, hipStream_t s)
+{
+    const int nb = (int)ceil_div(w.n, FB), groups = (int)ceil_div(m, 64);
+    launch_fill(scratch, 8 * (1 + groups), 0.0, s);
+    int *words = reinterpret_cast<int *>(scratch);
+    double *part = scratch + 8 * (1 + groups);
+    const unsigned grid = (unsigned)std::min<int64_t>((int64_t)nb * groups, 512);
+    switch (w.b) {
+    case 128: flow_rhs_kernel<128><<<grid, 256, 0, s>>>(w.tiles, w.dinv, st, nb, w.nt, groups, words, part); break;
+    case 256: flow_rhs_kernel<256><<<grid, 256, 0, s>>>(w.tiles, w.dinv, st, nb, w.nt, groups, words, part); break;
+    case 384: flow_rhs_kernel<384><<<grid, 256, 0, s>>>(w.tiles, w.dinv, st, nb, w.nt, groups, words, part); break;
+    default: flow_rhs_kernel<512><<<grid, 256, 0, s>>>(w.tiles, w.dinv, st, nb, w.nt, groups, words, part); break;
+    }
+    flow_rhs_sum_kernel<<<groups, 64, 0, s>>>(part, nb, groups, m, theta1, var);
 }
 
 }  // namespace gl

@@ -295,49 +295,6 @@ void launch_tiles_to_dense(const double *tiles, int b, int64_t n, double *out, i
     tiles_to_dense_kernel<<<grid, 256, 0, s>>>(tiles, b, n, out, ld);
 }
 
-// Kriging variances from the solved right-hand sides U (layout of st):
-// part[(c·nt + i)·b + r] = Σ_p U(c, i)[r, p]² per tile (one workgroup per
-// tile, threads along r), then var[c·b + r] = θ1 - Σ_i part[...] in tile
-// order (fixed order, deterministic).
-template <int B>
-__global__ __launch_bounds__(256) void rhs_sq_partial_kernel(const double *__restrict__ st, double *__restrict__ part)
-{
-    const int64_t t = blockIdx.x;
-    const double *T = st + t * (int64_t)B * B;
-    for (int r = threadIdx.x; r < B; r += 256) {
-        double acc = 0.0;
-        for (int p = 0; p < B; ++p) {
-            const double u = T[(int64_t)p * B + r];
-            acc += u * u;
-        }
-        part[t * B + r] = acc;
-    }
-}
-
-__global__ void rhs_var_kernel(const double *__restrict__ part, int64_t nt, int b, int64_t m, double theta1,
-                               double *__restrict__ var)
-{
-    const int64_t kn = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (kn >= m) return;
-    const int64_t c = kn / b, r = kn % b;
-    double acc = 0.0;
-    for (int64_t i = 0; i < nt; ++i) acc += part[(c * nt + i) * b + r];
-    var[kn] = theta1 - acc;
-}
-
-void launch_rhs_variance(const double *st, int b, int64_t nt, int64_t chunks, int64_t m, double theta1,
-                         double *part, double *var, hipStream_t s)
-{
-    const unsigned grid = (unsigned)(chunks * nt);
-    switch (b) {
-    case 128: rhs_sq_partial_kernel<128><<<grid, 256, 0, s>>>(st, part); break;
-    case 256: rhs_sq_partial_kernel<256><<<grid, 256, 0, s>>>(st, part); break;
-    case 384: rhs_sq_partial_kernel<384><<<grid, 256, 0, s>>>(st, part); break;
-    default: rhs_sq_partial_kernel<512><<<grid, 256, 0, s>>>(st, part); break;
-    }
-    rhs_var_kernel<<<(unsigned)ceil_div(m, 256), 256, 0, s>>>(part, nt, b, m, theta1, var);
-}
-
 // Cross-validation helpers: gather three arrays through an index list, and
 // the mean squared difference of two vectors (one workgroup, fixed order).
 __global__ void gather3_kernel(const double *__restrict__ a, const double *__restrict__ b,

@@ -266,41 +266,4 @@ void launch_trailing_list(double *tiles, int b, int64_t k, const int2 *list, int
         launch_trailing_list_t<false>(tiles, b, k, list, count, info, critical, s);
 }
 
-// Many right-hand sides, update after diagonal step k (layout of st as for
-// the multi-RHS diagonal solve): S(c, i) -= U(c, k) L_ikᵀ for every chunk c
-// and tile row i > k.  Blocks of one tile row i (sharing L_ik) are adjacent.
-template <int B>
-__global__ __launch_bounds__(256, 2) void mrhs_update_kernel(const double *__restrict__ tiles, double *__restrict__ st,
-                                                             int64_t nt, int64_t k, int64_t chunks, int64_t nblocks)
-{
-    constexpr int SB = B / GB;
-    constexpr int SUB = SB * SB;
-    const int64_t G = gridDim.x;
-    const int64_t g = blockIdx.x;
-    const int64_t lid = (g & 7) * (G >> 3) + (g >> 3);
-    if (lid >= nblocks) return;
-    const int sub = (int)(lid % SUB);
-    const int64_t tc = lid / SUB;
-    const int64_t c = tc % chunks;
-    const int64_t i = k + 1 + tc / chunks;
-    const int64_t bb = (int64_t)B * B;
-    trailing_core<B>(st + (c * nt + k) * bb, tiles + tile_offset(i, k, B), st + (c * nt + i) * bb, sub / SB,
-                     sub % SB);
-}
-
-void launch_mrhs_update(const double *tiles, double *st, int b, int64_t nt, int64_t k, int64_t chunks,
-                        hipStream_t s)
-{
-    const int64_t m = nt - k - 1;
-    if (m <= 0) return;
-    const int64_t nblocks = m * chunks * (b / GB) * (b / GB);
-    const int64_t grid = ceil_div(nblocks, 8) * 8;
-    switch (b) {
-    case 128: mrhs_update_kernel<128><<<(unsigned)grid, 256, 0, s>>>(tiles, st, nt, k, chunks, nblocks); break;
-    case 256: mrhs_update_kernel<256><<<(unsigned)grid, 256, 0, s>>>(tiles, st, nt, k, chunks, nblocks); break;
-    case 384: mrhs_update_kernel<384><<<(unsigned)grid, 256, 0, s>>>(tiles, st, nt, k, chunks, nblocks); break;
-    default: mrhs_update_kernel<512><<<(unsigned)grid, 256, 0, s>>>(tiles, st, nt, k, chunks, nblocks); break;
-    }
-}
-
 }  // namespace gl

@@ -152,28 +152,4 @@ void launch_trsm(double *tiles, int b, int64_t nt, int64_t k, const double *dinv
     }
 }
 
-// Many right-hand sides (kriging variances, Eq. 4): U = L⁻¹ S is solved in
-// the transposed form Uᵀ L_kkᵀ = Sᵀ, the panel form above.  st holds chunks
-// of b right-hand sides as nt tiles each (tile (c, i): b×b column-major, row
-// = right-hand side, column = location of tile i).  Diagonal step k solves
-// tile (c, k) of every chunk c.
-template <int B>
-__global__ __launch_bounds__(256) void mrhs_diag_kernel(const double *__restrict__ tiles, double *__restrict__ st,
-                                                        int64_t nt, int64_t k, const double *__restrict__ dinv)
-{
-    trsm_core<B>(tiles + tile_offset(k, k, B), st + ((int64_t)blockIdx.x * nt + k) * B * B, dinv, blockIdx.y);
-}
-
-void launch_mrhs_diag(const double *tiles, double *st, int b, int64_t nt, int64_t k, const double *dinv,
-                      int64_t chunks, hipStream_t s)
-{
-    dim3 grid((unsigned)chunks, (unsigned)(b / TB));
-    switch (b) {
-    case 128: mrhs_diag_kernel<128><<<grid, 256, 0, s>>>(tiles, st, nt, k, dinv); break;
-    case 256: mrhs_diag_kernel<256><<<grid, 256, 0, s>>>(tiles, st, nt, k, dinv); break;
-    case 384: mrhs_diag_kernel<384><<<grid, 256, 0, s>>>(tiles, st, nt, k, dinv); break;
-    default: mrhs_diag_kernel<512><<<grid, 256, 0, s>>>(tiles, st, nt, k, dinv); break;
-    }
-}
-
 }  // namespace gl

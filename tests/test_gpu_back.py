@@ -38,3 +38,27 @@ def test_backward_solve_through_kriging(n, tile):
     want, info = oracle.krige(x, y, z, xn, yn, theta)
     assert info == 0
     assert np.max(np.abs(got - want)) <= 1e-9 * np.max(np.abs(z))
+
+
+@pytest.mark.parametrize("n,tile,m", [(1, 128, 1), (128, 128, 64), (129, 256, 63), (385, 512, 65), (700, 384, 130),
+                                      (900, 128, 1061)])
+def test_variances_at_block_edges(n, tile, m):
+    """The one-launch right-hand-side solve (64 of them per block row): against
+    the oracle at the variance parity bound, 1e-15 κ(Σ) and at least 1e-10."""
+    import paper_1708_02835_amd as g
+    theta = (1.3, 0.1, 0.5)
+    x, y = geoinputs.jittered_grid(n, 9)
+    z = geoinputs.normal_vector(n, 9)
+    xn, yn = geoinputs.uniform_points(m, 9)
+    print(f"variances n={n} tile={tile} m={m}", flush=True)
+    with g.Context(0) as ctx:
+        r = g.loglik_eval(ctx, dev(x), dev(y), dev(z), theta, g.gl_opts_default(tile=tile, keep_factor=1))
+        assert r["status"] == g.GL_OK
+        pred, var = g.krige_predict(ctx, r["factor"], dev(xn), dev(yn), return_variance=True)
+        pred, var = pred.cpu().numpy(), var.cpu().numpy()
+        g.gl_factor_release(ctx, r["factor"])
+    want, wvar, info = oracle.krige(x, y, z, xn, yn, theta, return_variance=True)
+    assert info == 0
+    tol = max(1e-10, 1e-15 * np.linalg.cond(oracle.cov_symmetric(x, y, theta)))
+    assert np.max(np.abs(pred - want)) <= 1e-9 * np.max(np.abs(z))
+    assert np.max(np.abs(var - wvar)) <= tol * theta[0]
