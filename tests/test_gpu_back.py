@@ -62,3 +62,28 @@ def test_variances_at_block_edges(n, tile, m):
     tol = max(1e-10, 1e-15 * np.linalg.cond(oracle.cov_symmetric(x, y, theta)))
     assert np.max(np.abs(pred - want)) <= 1e-9 * np.max(np.abs(z))
     assert np.max(np.abs(var - wvar)) <= tol * theta[0]
+
+
+@pytest.mark.parametrize("metric,t3", [(0, 0.5), (0, 1.0), (1, 0.8)])
+def test_grouped_kriging_sums_equal_single_ones(metric, t3):
+    """2,050 new locations over two chunks of observed points take the kernel
+    that sums four at a time, half of them the one that sums one: the same
+    order per location, so the same bits."""
+    import paper_1708_02835_amd as g
+    n, m = 4097, 2050
+    x, y = geoinputs.jittered_grid(n, 10)
+    xn, yn = geoinputs.uniform_points(m, 10)
+    z = geoinputs.normal_vector(n, 10)
+    theta = (1.3, 300.0 if metric else 0.03, t3)
+    if metric:
+        x, y, xn, yn = -100 + 15 * x, 30 + 15 * y, -100 + 15 * xn, 30 + 15 * yn
+    o = dict(metric=metric, radius=6371.0)
+    print(f"grouped kriging metric={metric} t3={t3}", flush=True)
+    with g.Context(0) as ctx:
+        r = g.loglik_eval(ctx, dev(x), dev(y), dev(z), theta, g.gl_opts_default(keep_factor=1, **o))
+        assert r["status"] == g.GL_OK
+        whole = g.krige_predict(ctx, r["factor"], dev(xn), dev(yn))
+        h = m // 2
+        parts = [g.krige_predict(ctx, r["factor"], dev(xn[a:a + h]), dev(yn[a:a + h])) for a in (0, h)]
+        assert torch.equal(whole, torch.cat(parts))
+        g.gl_factor_release(ctx, r["factor"])
