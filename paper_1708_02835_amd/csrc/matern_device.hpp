@@ -56,6 +56,10 @@ __host__ __device__ inline double plain_rcp(double x)
 #endif
 }
 
+// The functions below write their fused operations out and allow no others:
+// left to the compiler, either product of a sum of two may be the one that is
+// not rounded, and kernels that should agree bit for bit would not.
+
 // Zero, as a value the compiler knows nothing about: an index with it keeps
 // the constants of the loops below in LDS.  They do not change from element
 // to element, and hoisted out of a caller's loop they would take hundreds of
@@ -150,18 +154,21 @@ template <bool TAB>
 __host__ __device__ inline void bessel_k_temme(const MaternSetup &s, double x, double xi, double lx, double &k0,
                                                double &k1, const BesselTab *tab)
 {
+#pragma clang fp contract(off)
     const double mu = s.mu;
     const double sig = mu * lx;
     const double e = exp(sig), ei = plain_rcp(e);
     double shs;  // sinh(σ)/σ
     if (fabs(sig) < 0.1) {
         const double q = sig * sig;  // Taylor series to σ⁸, remainder below 3e-18
-        shs = 1.0 + q * (1.0 / 6.0) *
-                        (1.0 + q * (1.0 / 20.0) * (1.0 + q * (1.0 / 42.0) * (1.0 + q * (1.0 / 72.0))));
+        shs = fma(q, 1.0 / 72.0, 1.0);
+        shs = fma(q * (1.0 / 42.0), shs, 1.0);
+        shs = fma(q * (1.0 / 20.0), shs, 1.0);
+        shs = fma(q * (1.0 / 6.0), shs, 1.0);
     } else {
         shs = 0.5 * (e - ei) * plain_rcp(sig);
     }
-    double f = s.fact * (0.5 * (e + ei) * s.g1 + shs * lx * s.g2);
+    double f = s.fact * fma(0.5 * (e + ei), s.g1, shs * lx * s.g2);
     double p = e * s.hgp;   // ½ (x/2)^-μ Γ(1+μ)
     double q = ei * s.hgm;  // ½ (x/2)^μ Γ(1-μ)
     double c = 1.0;
@@ -190,12 +197,12 @@ __host__ __device__ inline void bessel_k_temme(const MaternSetup &s, double x, d
             c *= d * rk;
             p *= rm;
             q *= rp;
-            t0 = c * f;
-            t1 = c * fma(-dk, f, p);
-            sum0 += t0;
-            sum1 += t1;
+            t0 = f;
+            t1 = fma(-dk, f, p);
+            sum0 = fma(c, t0, sum0);
+            sum1 = fma(c, t1, sum1);
         }
-        if (fabs(t0) < 1e-17 * fabs(sum0) && fabs(t1) < 1e-17 * fabs(sum1)) break;
+        if (fabs(c * t0) < 1e-17 * fabs(sum0) && fabs(c * t1) < 1e-17 * fabs(sum1)) break;
     }
     k0 = sum0;
     k1 = 2.0 * sum1 * xi;
@@ -206,6 +213,7 @@ template <bool TAB>
 __host__ __device__ inline void bessel_k_miller_scaled(const MaternSetup &s, double x, double xi, double &k0, double &k1,
                                                        const BesselTab *tab)
 {
+#pragma clang fp contract(off)
     const double mu2 = s.mu * s.mu;
     int kmax = (int)(8.0 + 140.0 * xi) + 3;
     kmax = (kmax < GL_MILLER_MAX ? kmax : GL_MILLER_MAX) & ~3;  // whole groups of four
@@ -236,12 +244,13 @@ __host__ __device__ inline void bessel_k_miller_scaled(const MaternSetup &s, dou
     }
     const double r0 = z1 * plain_rcp(z0);
     k0 = sqrt(0.5 * M_PI * xi) * z0 * plain_rcp(t);  // over S = t / z0
-    k1 = k0 * (s.mu + 0.5 + x - (0.25 - mu2) * r0) * xi;
+    k1 = k0 * fma(mu2 - 0.25, r0, s.mu + 0.5 + x) * xi;
 }
 
 // The half-integer closed forms at x = r/θ2 (s.kind 1, 2, 3).
 __host__ __device__ inline double matern_closed(const MaternSetup &s, double x)
 {
+#pragma clang fp contract(off)
     switch (s.kind) {
     case 1: return s.theta1 * exp(-x);
     case 2: return s.theta1 * (1.0 + x) * exp(-x);
@@ -265,6 +274,7 @@ __host__ __device__ inline double matern_eval_closed(const MaternSetup &s, doubl
 template <bool TAB>
 __host__ __device__ inline double matern_eval_t(const MaternSetup &s, double r, const BesselTab *tab)
 {
+#pragma clang fp contract(off)
     if (r == 0.0) return s.theta1;
     const double x = r / s.theta2;
     // Past x = 2000 the correlation C/θ1 is below e^-1600 for every ν <= 50,
@@ -299,7 +309,7 @@ __host__ __device__ inline double matern_eval_t(const MaternSetup &s, double r, 
             lsc += 900.0 * M_LN2;
         }
         for (int i = 1; i < s.nl; ++i) {
-            double kc = ka + (2.0 * (s.mu + i) * xi) * kb;
+            double kc = fma(2.0 * (s.mu + i) * xi, kb, ka);
             ka = kb;
             kb = kc;
             if (kb > 0x1p500) {
@@ -310,8 +320,7 @@ __host__ __device__ inline double matern_eval_t(const MaternSetup &s, double r, 
         }
         knu = kb;
     }
-    if (small) return s.pref * exp(s.nu * lgx + lsc) * knu;
-    return s.pref * exp(s.nu * lgx - xc + lsc) * knu;
+    return s.pref * exp(fma(s.nu, lgx, small ? lsc : lsc - xc)) * knu;
 }
 
 __host__ __device__ inline double matern_eval(const MaternSetup &s, double r) { return matern_eval_t<false>(s, r, nullptr); }
@@ -322,8 +331,9 @@ __device__ inline double matern_eval(const MaternSetup &s, double r, const Besse
 
 __host__ __device__ inline double dist2d(double x1, double y1, double x2, double y2)
 {
+#pragma clang fp contract(off)
     double dx = x1 - x2, dy = y1 - y2;
-    return sqrt(dx * dx + dy * dy);
+    return sqrt(fma(dx, dx, dy * dy));
 }
 
 // Great-circle distance on a sphere of radius rho (Sec. 7.4): x = longitude,
@@ -332,11 +342,11 @@ __host__ __device__ inline double dist2d(double x1, double y1, double x2, double
 __host__ __device__ inline double gcd_dist_cos(double x1, double y1, double c1, double x2, double y2, double c2,
                                                double rho)  // c: cos of the latitude
 {
+#pragma clang fp contract(off)
     const double deg = M_PI / 180.0;
-    const double p1 = y1 * deg, p2 = y2 * deg;
-    const double sp = sin(0.5 * (p2 - p1));
+    const double sp = sin(0.5 * ((y2 - y1) * deg));
     const double sl = sin(0.5 * ((x2 - x1) * deg));
-    double h = sp * sp + c1 * c2 * sl * sl;
+    double h = fma(c1 * c2 * sl, sl, sp * sp);
     h = fmin(fmax(h, 0.0), 1.0);
     return 2.0 * rho * asin(sqrt(h));
 }
