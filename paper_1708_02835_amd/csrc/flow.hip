@@ -18,12 +18,22 @@
 // first.  Every task depends only on tasks with smaller tickets, and a ticket
 // is only held by a running workgroup, so the smallest unfinished task can
 // always proceed: no co-residency of the grid is assumed, and every wait ends.
-// Progress words (agent-scope, release after the data, acquire before its
-// use): prog[i] = blocks of row i that are final (row i's blocks finish in
-// column order, since each needs the one before), ready[j] = 1 once L_jj's
-// first 64 columns and D_0⁻¹ are final, 2 with the second half, 3 with w_j.
+// Progress words: prog[i] = 64-column halves of row i's blocks that are final
+// (they finish in column order, since each block needs the one before),
+// ready[j] = 1 once L_jj's first 64 columns and D_0⁻¹ are final, 2 with the
+// second half, 3 with w_j, vdone[i] = blocks whose part of v_i is subtracted.
+// What a word announces is stored through the XCD's cache to the agent's
+// coherence point (agent-scope stores), the word follows once those stores are
+// acknowledged, and a reader invalidates its caches after it has seen the word.
 // A pivot that is not positive stores its column in *info; workgroups that
 // wait see it and leave.
+//
+// The chain is diagonal block j -> block (j + 1, j) -> the last panel of
+// diagonal block j + 1, with block (j + 2, j), which block (j + 2, j + 1) needs,
+// close behind.  Their workgroups ask the other workgroup on their CU to stand
+// still meanwhile (see CuClaim); blocks near the diagonal announce their first
+// half early, so that diagonal block j + 1 has only 64 columns left to add when
+// the second arrives; and the forward solve stays off the chain.
 //
 // Four waves of 32 rows × 128 columns: a wave then holds whole rows of T, and
 // since a 16x16x4 result has the lane layout of a B operand, the triangular
@@ -34,10 +44,14 @@
 // The sequence of operations on every element is that of the step schedule
 // (potrf.hip, trsm.hip, trailing.hip, solve.hip), so both give the same bits.
 //
-// Bound by the matrix cores from about n = 12,000 up (67.6 TFLOP/s of 78.6 at
-// n = 40,000, 69 at n = 100,000) and by the chain of diagonal blocks below.
-// Whole evaluations, step schedule and this: n = 400 480 and 252 µs, n = 1,600
-// 1.48 and 0.67 ms, n = 8,100 11.2 and 4.6 ms, n = 40,000 373 and 316 ms.
+// Bound by the matrix cores from about n = 12,000 up (69 TFLOP/s of 78.6 at
+// n = 40,000 and 100,000) and by the chain below: 36.5 µs per 128 columns, of
+// which the two 64×64 factors take 16, the panel and update between them 5.7,
+// L_j+1,j 4.5 after the second half of L_jj and the last 64 columns of the next
+// diagonal block 7 (46.6 before the claims, the early halves and the forward
+// solve off the chain; then 71 at n = 8,100 where it shared the CUs, 55 now).
+// Whole evaluations, step schedule and this: n = 400 480 and 185 µs, n = 1,600
+// 1.49 and 0.51 ms, n = 8,100 11.2 and 3.9 ms, n = 40,000 373 and 309 ms.
 #include <algorithm>
 
 #include "batch.hpp"
@@ -53,13 +67,13 @@ namespace {
 constexpr int FB = 128;      // block edge
 constexpr int FK = 16;       // columns per staged chunk
 constexpr int FP = FB + 16;  // LDS pitch of a staged chunk (bank spread, as trailing.hip)
-constexpr int FC = FB / FK;  // chunks per block
+constexpr int CHAIN = 2;     // blocks below the diagonal that count as the chain's
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 struct FlowProb {
     double *tiles, *v, *dinv, *logsum, *quad;
     int64_t *info;
-    int *words;   // ticket, then prog and ready, `stride` ints apart
+    int *words;   // ticket, then prog, ready and vdone, `stride` ints apart
     int64_t n;
     int nb, pad;  // blocks with rows below n; all-padding blocks after them
     int stride, solve;
@@ -73,8 +87,37 @@ struct FlowShared {
     int fail, word;
 };
 
-__device__ __forceinline__ int peek(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void post(int *p, int x) { __hip_atomic_store(p, x, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T>
+__device__ __forceinline__ T peek(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// A store to the coherence point; words are posted after settle().
+template <class T>
+__device__ __forceinline__ void post(T *p, T x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+constexpr int BUF_AGENT = 16;  // the same for a buffer store (sc1)
+
+// Workgroups in the serial phase of a chain task, per CU.  Another workgroup's
+// binary64 matrix instructions hold the SIMD's pipe for 64 cycles each, which
+// stretched a diagonal block from 25 to 95 µs, so workgroups in the K loop of
+// other tasks wait while their CU is claimed (standing still for some 30 µs,
+// one of 512).  A claimant waits for nobody who might stand still: for none, or
+// in its solve for diagonal block j, which has already announced its first half.
+__device__ int flow_cu_claims[8 * 256];
+struct CuClaim {
+    int *count;
+    __device__ __forceinline__ CuClaim()
+    {
+        // HW_ID bits 8..15: CU, shader array and engine; XCC_ID: the XCD
+        const int cu = __builtin_amdgcn_s_getreg(4 | (8 << 6) | (7 << 11));
+        const int xcd = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (2 << 11));
+        count = flow_cu_claims + xcd * 256 + cu;
+    }
+    __device__ __forceinline__ void take() const { add(1); }
+    __device__ __forceinline__ void drop() const { add(-1); }
+    __device__ __forceinline__ bool held() const { return peek(count) > 0; }
+    __device__ __forceinline__ void add(int d) const
+    {
+        if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(count, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
 
 // Waits until min(*a, *b) >= want and returns it; -1 when the factorisation
 // has failed (info, if not NULL).  Called by every thread; one polls.
@@ -84,7 +127,7 @@ __device__ __forceinline__ int await(const int *a, const int *b, int want, const
     if (threadIdx.x == 0) {
         int x;
         while ((x = min(peek(a), peek(b))) < want) {
-            if (info && __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            if (info && peek(info) != 0) {
                 x = -1;
                 break;
             }
@@ -97,8 +140,8 @@ __device__ __forceinline__ int await(const int *a, const int *b, int want, const
     return sh.word;
 }
 
-// Every wave's stores so far are in the cache of its XCD when this returns;
-// the release of the thread that posts a progress word then publishes them.
+// Every wave's stores so far have been acknowledged when this returns, those at
+// agent scope from the coherence point: a word posted now announces them.
 __device__ __forceinline__ void settle()
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -136,11 +179,11 @@ __device__ __forceinline__ double staged(const double *s, int m, int c) { return
 
 // acc += rows of A times rows of B over the columns [c0, c1) (multiples of
 // FK), A of 64 NA and B of 128 rows, ld B; wave w has the NA 16-row blocks from
-// NA w.  DIAG (NA = 2): A == B, and its row blocks are w and 7 - w, columns up
-// to the diagonal only.
-template <int B, int NA, bool DIAG>
+// NA w.  Between chunks the workgroup stands still while `cu` is claimed, if
+// `yields`.
+template <int B, int NA>
 __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const double *__restrict__ Bp, int c0, int c1,
-                                           d4 (*acc)[8], double *buf)
+                                           d4 (*acc)[8], double *buf, const CuClaim &cu, bool yields)
 {
     auto As = reinterpret_cast<double(*)[FK][FP]>(buf);
     auto Bs = reinterpret_cast<double(*)[FK][FP]>(buf + 2 * FK * FP);
@@ -149,20 +192,20 @@ __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lc = tid >> 4;
     const int le = (tid & 15) * 2;
-    const int ra0 = DIAG ? wave * 16 : wave * 16 * NA, ra1 = DIAG ? (7 - wave) * 16 : wave * 32 + 16;
+    const int row0 = wave * 16 * NA + (lane & 15);
     d2 ra[4], rb[4];
     auto load = [&](int col) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if (q < 2 * NA) ra[q] = *reinterpret_cast<const d2 *>(Ap + (int64_t)(col + lc) * B + le + 32 * q);
-            if constexpr (!DIAG) rb[q] = *reinterpret_cast<const d2 *>(Bp + (int64_t)(col + lc) * B + le + 32 * q);
+            rb[q] = *reinterpret_cast<const d2 *>(Bp + (int64_t)(col + lc) * B + le + 32 * q);
         }
     };
     auto store = [&](int cur) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if (q < 2 * NA) *reinterpret_cast<d2 *>(&As[cur][lc][le + 32 * q]) = ra[q];
-            if constexpr (!DIAG) *reinterpret_cast<d2 *>(&Bs[cur][lc][le + 32 * q]) = rb[q];
+            *reinterpret_cast<d2 *>(&Bs[cur][lc][le + 32 * q]) = rb[q];
         }
     };
     load(c0);
@@ -170,25 +213,76 @@ __device__ __forceinline__ void accumulate(const double *__restrict__ Ap, const 
     __syncthreads();
     int cur = 0;
     for (int c = c0; c < c1; c += FK, cur ^= 1) {
+        bool held = false;
+        if (yields) held = cu.held();
         if (c + FK < c1) load(c + FK);
 #pragma unroll
         for (int kk = 0; kk < FK; kk += 4) {
             const double *arow = As[cur][kk + (lane >> 4)];
-            const double *brow = DIAG ? arow : Bs[cur][kk + (lane >> 4)];
-            const double a0 = arow[ra0 + (lane & 15)], a1 = NA > 1 ? arow[ra1 + (lane & 15)] : 0.0;
+            const double *brow = Bs[cur][kk + (lane >> 4)];
+            const double a0 = arow[row0], a1 = NA > 1 ? arow[row0 + 16] : 0.0;
             double bv[8];
 #pragma unroll
             for (int b = 0; b < 8; ++b) bv[b] = brow[b * 16 + (lane & 15)];
             // operands swapped: result row = block column, lane % 16 = block row
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                if (!DIAG || (b < 4 && b <= wave)) acc[0][b] = mfma_f64(bv[b], a0, acc[0][b]);
-                if (NA > 1 && (!DIAG || b < 4 || b <= 7 - wave)) acc[1][b] = mfma_f64(bv[b], a1, acc[1][b]);
+                acc[0][b] = mfma_f64(bv[b], a0, acc[0][b]);
+                if (NA > 1) acc[1][b] = mfma_f64(bv[b], a1, acc[1][b]);
             }
         }
         // the staging of the next chunk stays after this chunk's products
         __builtin_amdgcn_sched_barrier(0);
+        if (held)
+            while (cu.held()) __builtin_amdgcn_s_sleep(16);
         if (c + FK < c1) store(cur ^ 1);
+        __syncthreads();
+    }
+}
+
+// The same for the lower half of a diagonal block, A == B: wave w has the
+// 16-row blocks w and 7 - w, columns up to the diagonal.  [c0, c1) is in whole
+// 64s, staged four chunks at a time: with nine products per wave and four
+// columns, a chunk is computed faster than its loads come back.
+template <int B>
+__device__ __forceinline__ void accumulate_diag(const double *__restrict__ Ap, int c0, int c1, d4 (*acc)[8], double *buf)
+{
+    auto As = reinterpret_cast<double(*)[FP]>(buf);
+    const int tid = thread_index();
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = tid >> 4;
+    const int le = (tid & 15) * 2;
+    const int ra0 = wave * 16 + (lane & 15), ra1 = (7 - wave) * 16 + (lane & 15);
+    d2 ra[4][4];
+    auto load = [&](int col) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                ra[g][q] = *reinterpret_cast<const d2 *>(Ap + (int64_t)(col + FK * g + lc) * B + le + 32 * q);
+    };
+    load(c0);
+    for (int c = c0; c < c1; c += 4 * FK) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<d2 *>(&As[FK * g + lc][le + 32 * q]) = ra[g][q];
+        __syncthreads();
+        if (c + 4 * FK < c1) load(c + 4 * FK);
+#pragma unroll 4
+        for (int kk = 0; kk < 4 * FK; kk += 4) {
+            const double *arow = As[kk + (lane >> 4)];
+            const double a0 = arow[ra0], a1 = arow[ra1];
+            double bv[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) bv[b] = arow[b * 16 + (lane & 15)];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                if (b < 4 && b <= wave) acc[0][b] = mfma_f64(bv[b], a0, acc[0][b]);
+                if (b < 4 || b <= 7 - wave) acc[1][b] = mfma_f64(bv[b], a1, acc[1][b]);
+            }
+        }
         __syncthreads();
     }
 }
@@ -252,7 +346,9 @@ __device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowSh
     double *C = const_cast<double *>(Ai) + (int64_t)j * FB * B;
     const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(C, (short)0, FB * B * 8, 0x00020000);
     const int cvo = (mfma_row(lane, 0) * B + wave * 32 + mfma_col(lane)) * 8;
-    int *prog = p.words + 2 * p.stride, *ready = prog + p.nb * p.stride;
+    int *prog = p.words + 2 * p.stride, *ready = prog + (p.nb + j) * p.stride, *vdone = prog + (2 * p.nb + i) * p.stride;
+    const bool chain = i <= j + CHAIN;
+    const CuClaim cu;
 
     d4 acc[2][8];
 #pragma unroll
@@ -263,23 +359,26 @@ __device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowSh
             for (int r = 0; r < 4; ++r)
                 acc[a][b][r] = -__builtin_bit_cast(
                     double, __builtin_amdgcn_raw_buffer_load_b64(crs, cvo, ((b * 16 + 4 * r) * B + a * 16) * 8, 0));
-    for (int k = 0; k < j;) {
+    for (int k = 0; k < 2 * j;) {
         const int have = await(prog + i * p.stride, prog + j * p.stride, k + 1, p.info, sh);
         if (have < 0) return false;
-        const int e = min(have, j);
-        accumulate<B, 2, false>(Ai, Bj, k * FB, e * FB, acc, sh.buf);
+        const int e = min(have, 2 * j);
+        const bool last = chain && e == 2 * j;  // nothing left to wait for
+        if (last) cu.take();
+        accumulate<B, 2>(Ai, Bj, k * PB, e * PB, acc, sh.buf, cu, !last);
+        if (last) cu.drop();
         k = e;
     }
     // first 64 columns, then the second
     const double *Ljj = Bj + (int64_t)j * FB * B;
     const double *dv = p.dinv + (int64_t)j * 2 * PB * PB;
     double *s0 = sh.buf, *s1 = sh.buf + PB * PB;
-    if (await(ready + j * p.stride, ready + j * p.stride, 1, p.info, sh) < 0) return false;
+    if (await(ready, ready, 1, p.info, sh) < 0) return false;
+    if (chain) cu.take();
     stage64(dv, PB, s0);
     stage64(Ljj + PB, B, s1);
     __syncthreads();
     solve64<2, 0>(acc, [&](int m, int c) { return staged(s0, m, c); });
-    carry64<2>(acc, s1);
     auto put = [&](int h) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -289,33 +388,45 @@ __device__ __forceinline__ bool flow_off(const FlowProb &p, int i, int j, FlowSh
                 for (int r = 0; r < 4; ++r) {
                     const double x = acc[a][b][r];
                     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), crs, cvo,
-                                                          ((b * 16 + 4 * r) * B + a * 16) * 8, 0);
+                                                          ((b * 16 + 4 * r) * B + a * 16) * 8, BUF_AGENT);
                 }
     };
     put(0);
-    if (await(ready + j * p.stride, ready + j * p.stride, 2, p.info, sh) < 0) return false;
+    if (chain) {
+        settle();
+        if (tid == 0) post(prog + i * p.stride, 2 * j + 1);
+    }
+    carry64<2>(acc, s1);
+    if (await(ready, ready, 2, p.info, sh) < 0) {
+        if (chain) cu.drop();
+        return false;
+    }
     stage64(dv + PB * PB, PB, s0);
     __syncthreads();
     solve64<2, 4>(acc, [&](int m, int c) { return staged(s0, m, c); });
     put(4);
-    if (p.solve) {
-        if (await(ready + j * p.stride, ready + j * p.stride, 3, p.info, sh) < 0) return false;
-        if (tid < FB) sh.w[tid] = p.v[(int64_t)j * FB + tid];
-        __syncthreads();
+    settle();
+    if (tid == 0) post(prog + i * p.stride, 2 * j + 2);
+    if (chain) cu.drop();
+    if (!p.solve) return true;
+    if (await(ready, ready, 3, p.info, sh) < 0) return false;
+    if (await(vdone, vdone, j, p.info, sh) < 0) return false;
+    if (tid < FB) sh.w[tid] = peek(p.v + (int64_t)j * FB + tid);
+    __syncthreads();
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            double s = 0.0;
+    for (int a = 0; a < 2; ++a) {
+        double s = 0.0;
 #pragma unroll
-            for (int b = 0; b < 8; ++b)
+        for (int b = 0; b < 8; ++b)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) s = fma(acc[a][b][r], sh.w[b * 16 + mfma_row(lane, r)], s);
-            s += __shfl_xor(s, 16, 64);
-            s += __shfl_xor(s, 32, 64);
-            if (lane < 16) p.v[(int64_t)i * FB + wave * 32 + a * 16 + lane] -= s;
-        }
+            for (int r = 0; r < 4; ++r) s = fma(acc[a][b][r], sh.w[b * 16 + mfma_row(lane, r)], s);
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        double *vi = p.v + (int64_t)i * FB + wave * 32 + a * 16 + lane;
+        if (lane < 16) post(vi, peek(vi) - s);
     }
     settle();
-    if (tid == 0) post(prog + i * p.stride, j + 1);
+    if (tid == 0) post(vdone, j + 1);
     return true;
 }
 
@@ -331,7 +442,8 @@ __device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &
     double *C = const_cast<double *>(Aj) + (int64_t)j * FB * B;
     double *vj = p.v + (int64_t)j * FB;
     double *dv = p.dinv + (int64_t)j * 2 * PB * PB;
-    int *prog = p.words + 2 * p.stride, *ready = prog + (p.nb + j) * p.stride;
+    int *prog = p.words + 2 * p.stride, *ready = prog + (p.nb + j) * p.stride, *vdone = prog + (2 * p.nb + j) * p.stride;
+    const CuClaim cu;
     const int64_t rows = p.n - (int64_t)j * FB;  // rows that are not padding
     const int q = lane >> 4, r16 = lane & 15;
     const int rb0 = wave, rb1 = 7 - wave;  // 16-row blocks of this wave
@@ -344,13 +456,15 @@ __device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 acc[a][b][r] = -C[(int64_t)(b * 16 + mfma_row(lane, r)) * B + (a ? rb1 : rb0) * 16 + r16];
-    for (int k = 0; k < j;) {
+    for (int k = 0; k < 2 * j;) {
         const int have = await(prog + j * p.stride, prog + j * p.stride, k + 1, p.info, sh);
         if (have < 0) return false;
-        const int e = min(have, j);
-        accumulate<B, 2, true>(Aj, Aj, k * FB, e * FB, acc, sh.buf);
+        const int e = min(have, 2 * j);
+        if (e == 2 * j) cu.take();
+        accumulate_diag<B>(Aj, k * PB, e * PB, acc, sh.buf);
         k = e;
     }
+    if (j == 0) cu.take();
     auto X = reinterpret_cast<double(*)[PB + 1]>(sh.buf);                  // D_0, then X_10, then D_1⁻¹
     auto Y = reinterpret_cast<double(*)[PB + 1]>(sh.buf + PB * (PB + 1));  // D_0⁻¹, then D_1
 #pragma unroll
@@ -359,36 +473,26 @@ __device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &
 #pragma unroll
             for (int r = 0; r < 4; ++r) X[b * 16 + mfma_row(lane, r)][rb0 * 16 + r16] = -acc[0][b][r];
         }
-    if (tid < FB) sh.v[tid] = vj[tid];
     if (tid == 0) sh.fail = 0;
     __syncthreads();
     if (!factor_invert_64(X, Y, &sh.fail, (int64_t)j * FB, p.info)) {
         if (tid == 0) __threadfence();
+        cu.drop();
         return false;
     }
-    // L_00 and D_0⁻¹ out, the rows below by 16-row blocks, one per wave
+    // the rows below by 16-row blocks, one per wave; L_00, D_0⁻¹ and they go out
+    solve64<1, 0>(&acc[1], [&](int m, int c) { return Y[m][c]; });
     for (int e = tid; e < PB * PB; e += 256) {
         const int c = e >> 6, r = e & 63;
-        if (r >= c) C[(int64_t)c * B + r] = X[c][r];
-        dv[e] = r >= c ? Y[c][r] : 0.0;
+        if (r >= c) post(C + (int64_t)c * B + r, X[c][r]);
+        post(dv + e, r >= c ? Y[c][r] : 0.0);
     }
-    solve64<1, 0>(&acc[1], [&](int m, int c) { return Y[m][c]; });
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) C[(int64_t)(b * 16 + mfma_row(lane, r)) * B + rb1 * 16 + r16] = acc[1][b][r];
-    // w_0 = D_0⁻¹ v_0
-    const int vr = tid & 63, vg = tid >> 6;
-    if (p.solve) {
-        double s = 0.0;
-#pragma unroll
-        for (int m = 0; m < PB; m += 4) s = fma(m + vg <= vr ? Y[m + vg][vr] : 0.0, sh.v[m + vg], s);
-        sh.part[vg][vr] = s;
-    }
-    double lg = wave == 0 && lane < rows ? log(X[lane][lane]) : 0.0;
-    settle();
-    if (tid == 192) post(ready, 1);
-    if (p.solve && tid < PB) sh.w[vr] = (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]);
+        for (int r = 0; r < 4; ++r) post(C + (int64_t)(b * 16 + mfma_row(lane, r)) * B + rb1 * 16 + r16, acc[1][b][r]);
+    double lg = wave == 0 ? X[lane][lane] : 1.0;
+    __syncthreads();
     // X_10 to LDS, -D_1 += X_10 X_10ᵀ
 #pragma unroll
     for (int b = 0; b < 4; ++b)
@@ -410,56 +514,78 @@ __device__ __forceinline__ bool flow_diag(const FlowProb &p, int j, FlowShared &
 #pragma unroll
             for (int r = 0; r < 4; ++r) Y[16 * cb + mfma_row(lane, r)][(3 - wave) * 16 + r16] = -acc[1][4 + cb][r];
         }
-    if (p.solve) {
-        // v_1 - L_10 w_0
-        double s = 0.0;
-#pragma unroll
-        for (int c = 0; c < PB; c += 4) s = fma(X[c + vg][vr], sh.w[c + vg], s);
-        sh.part[vg][vr] = s;
-    }
-    __syncthreads();
-    if (p.solve && tid < PB) sh.v[PB + vr] -= (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]);
+    settle();
+    if (tid == 0) post(ready, 1);
     if (!factor_invert_64(Y, X, &sh.fail, (int64_t)j * FB + PB, p.info)) {
         if (tid == 0) __threadfence();
+        cu.drop();
         return false;
     }
     for (int e = tid; e < PB * PB; e += 256) {
         const int c = e >> 6, r = e & 63;
-        if (r >= c) C[(int64_t)(PB + c) * B + PB + r] = Y[c][r];
-        dv[PB * PB + e] = r >= c ? X[c][r] : 0.0;
+        if (r >= c) post(C + (int64_t)(PB + c) * B + PB + r, Y[c][r]);
+        post(dv + PB * PB + e, r >= c ? X[c][r] : 0.0);
     }
     settle();
-    if (tid == 192) post(ready, 2);
-    if (wave == 1) lg = PB + lane < rows ? log(Y[lane][lane]) : 0.0;
-    if (p.solve) {
-        double s = 0.0;
+    if (tid == 0) post(ready, 2);
+    cu.drop();
+    if (!p.solve) return true;
+    // off the chain: w_0 = D_0⁻¹ v_0, w_1 = D_1⁻¹ (v_1 - L_10 w_0), each product
+    // over four thread groups
+    const int vr = tid & 63, vg = tid >> 6;
+    if (wave == 1) lg = Y[lane][lane];
+    lg = tid < FB && tid < rows ? log(lg) : 0.0;
+    if (await(vdone, vdone, j, p.info, sh) < 0) return false;
+    double d0[16], l10[16];
 #pragma unroll
-        for (int m = 0; m < PB; m += 4) s = fma(m + vg <= vr ? X[m + vg][vr] : 0.0, sh.v[PB + m + vg], s);
-        sh.part[vg][vr] = s;
-        __syncthreads();
-        if (tid < PB) sh.w[PB + vr] = (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]);
-        __syncthreads();
-        const double w = tid < FB ? sh.w[tid] : 0.0;
-        if (tid < FB) vj[tid] = w;
-        // the block's parts, added in block order (the storage tile's first block starts the sums)
-        double part = wave_sum(lg);
-        if (lane == 0 && wave < 2) sh.red[wave] = part;
-        part = wave_sum(tid < rows ? w * w : 0.0);
-        if (lane == 0 && wave < 2) sh.red[2 + wave] = part;
-        __syncthreads();
-        if (tid == 0) {
-            const int t = j / S;
-            double ls = 2.0 * (sh.red[0] + sh.red[1]), qs = sh.red[2] + sh.red[3];
-            if (j % S) {
-                ls = p.logsum[t] + ls;
-                qs = p.quad[t] + qs;
-            }
-            p.logsum[t] = ls;
-            p.quad[t] = qs;
-        }
-        settle();
-        if (tid == 0) post(ready, 3);
+    for (int m = 0; m < 16; ++m) {
+        d0[m] = dv[(4 * m + vg) * PB + vr];
+        l10[m] = C[(int64_t)(4 * m + vg) * B + PB + vr];
     }
+    if (tid < FB) sh.v[tid] = peek(vj + tid);
+    __syncthreads();
+    auto total = [&] { return (sh.part[0][vr] + sh.part[1][vr]) + (sh.part[2][vr] + sh.part[3][vr]); };
+    double s = 0.0;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) s = fma(d0[m], sh.v[4 * m + vg], s);
+    sh.part[vg][vr] = s;
+    __syncthreads();
+    if (tid < PB) sh.w[vr] = total();
+    __syncthreads();
+    s = 0.0;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) s = fma(l10[m], sh.w[4 * m + vg], s);
+    sh.part[vg][vr] = s;
+    __syncthreads();
+    if (tid < PB) sh.v[PB + vr] -= total();
+    __syncthreads();
+    s = 0.0;
+#pragma unroll
+    for (int m = 0; m < PB; m += 4) s = fma(m + vg <= vr ? X[m + vg][vr] : 0.0, sh.v[PB + m + vg], s);
+    sh.part[vg][vr] = s;
+    __syncthreads();
+    if (tid < PB) sh.w[PB + vr] = total();
+    __syncthreads();
+    const double w = tid < FB ? sh.w[tid] : 0.0;
+    if (tid < FB) post(vj + tid, w);
+    // the block's parts, added in block order (the storage tile's first block starts the sums)
+    double part = wave_sum(lg);
+    if (lane == 0 && wave < 2) sh.red[wave] = part;
+    part = wave_sum(tid < rows ? w * w : 0.0);
+    if (lane == 0 && wave < 2) sh.red[2 + wave] = part;
+    __syncthreads();
+    if (tid == 0) {
+        const int t = j / S;
+        double ls = 2.0 * (sh.red[0] + sh.red[1]), qs = sh.red[2] + sh.red[3];
+        if (j % S) {
+            ls = peek(p.logsum + t) + ls;
+            qs = peek(p.quad + t) + qs;
+        }
+        post(p.logsum + t, ls);
+        post(p.quad + t, qs);
+    }
+    settle();
+    if (tid == 0) post(ready, 3);
     return true;
 }
 
@@ -483,7 +609,7 @@ __device__ __forceinline__ bool flow_task(const FlowProb &p, int i, int j, FlowS
         __builtin_amdgcn_s_setprio(3);  // the critical chain
         return flow_diag<B>(p, j, sh);
     }
-    if (i == j + 1) __builtin_amdgcn_s_setprio(2);
+    if (i <= j + CHAIN) __builtin_amdgcn_s_setprio(2);
     else __builtin_amdgcn_s_setprio(0);
     return flow_off<B>(p, i, j, sh);
 }
@@ -609,6 +735,7 @@ __global__ __launch_bounds__(256, 2) void flow_rhs_kernel(const double *__restri
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         int *prog = words + 16 * (1 + R);
+        const CuClaim cu;
         double *A = st + (R / RS) * nt * B * B + (R % RS) * 64;
         double *C = A + (int64_t)j * FB * B;
         const double *Bj = tiles + tile_offset(j / S, 0, B) + (j % S) * FB;
@@ -622,7 +749,7 @@ __global__ __launch_bounds__(256, 2) void flow_rhs_kernel(const double *__restri
             for (int r = 0; r < 4; ++r) acc[0][b][r] = -C[at + (int64_t)(b * 16 + 4 * r) * B];
         for (int k = 0; k < j;) {
             const int e = min(await(prog, prog, k + 1, nullptr, sh), j);
-            accumulate<B, 1, false>(A, Bj, k * FB, e * FB, acc, sh.buf);
+            accumulate<B, 1>(A, Bj, k * FB, e * FB, acc, sh.buf, cu, false);
             k = e;
         }
         __syncthreads();
@@ -641,7 +768,7 @@ __global__ __launch_bounds__(256, 2) void flow_rhs_kernel(const double *__restri
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const double x = acc[0][b][r];
-                C[at + (int64_t)(b * 16 + 4 * r) * B] = x;
+                post(C + at + (int64_t)(b * 16 + 4 * r) * B, x);
                 q = fma(x, x, q);
             }
         settle();

@@ -64,7 +64,7 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
     const int64_t block = bt * b;  // uniform block length (the likelihood's), for the reported column
     // layout (in doubles): descriptors | total | solve words | per-block results, info |
     // per block: tiles, x, y, v, logsum, quad, dinv, progress words | reordered inputs, keys
-    auto word_doubles = [](int64_t n) { return (size_t)flow_words(n, flow_stride(n)) / 2; };
+    auto word_doubles = [](int64_t n) { return (size_t)(flow_words(n, flow_stride(n)) + 1) / 2; };
     const size_t desc_d = ((size_t)nblk * sizeof(BatchReq) + 15) / 16 * 2;
     size_t off = desc_d + 8 + BACK_WORDS + 8 * (size_t)nblk + 8 * (size_t)nblk;
     std::vector<size_t> boff(nblk);
