@@ -21,6 +21,7 @@
 // The diagonal block is solved by the inverses of its two 64×64 blocks:
 //   x_1 = D_1⁻ᵀ y_1,  x_0 = D_0⁻ᵀ (y_0 - L_10ᵀ x_1).
 // Sums have a fixed order.
+#include "batch.hpp"
 #include "common.hpp"
 #include "engine.hpp"
 #include "mfma.hpp"
@@ -48,12 +49,12 @@ __device__ __forceinline__ double sum8(double v)
     return v + __shfl_xor(v, 4, 64);
 }
 
+// The next column of one solve; words: ticket and number of solved columns, zero at first.
 template <int B>
-__global__ __launch_bounds__(256, 2) void back_kernel(const double *__restrict__ tiles, const double *__restrict__ dinv,
-                                                      double *x, int nb, int *words)
+__device__ __forceinline__ void back_column(const double *__restrict__ tiles, const double *__restrict__ dinv, double *x,
+                                            int nb, int *words, BackShared &sh)
 {
     constexpr int S = B / KB;
-    __shared__ BackShared sh;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -158,6 +159,32 @@ __global__ __launch_bounds__(256, 2) void back_kernel(const double *__restrict__
     if (tid == 0) __hip_atomic_store(solved, nb - j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+template <int B>
+__global__ __launch_bounds__(256, 2) void back_kernel(const double *__restrict__ tiles, const double *__restrict__ dinv,
+                                                      double *x, int nb, int *words)
+{
+    __shared__ BackShared sh;
+    back_column<B>(tiles, dinv, x, nb, words, sh);
+}
+
+__global__ void back_clear_kernel(const BatchReq *__restrict__ d, int count)
+{
+    const int r = blockIdx.x * 256 + threadIdx.x;
+    if (r < count) d[r].words[0] = d[r].words[1] = 0;
+}
+
+// Workgroups count·i .. count·i + count - 1 hold a column of each solve: the
+// chains run side by side.  Failed factorisations are passed over.
+template <int B>
+__global__ __launch_bounds__(256, 2) void back_batched_kernel(const BatchReq *__restrict__ d, int count)
+{
+    __shared__ BackShared sh;
+    const BatchReq &q = d[blockIdx.x % count];
+    const int nb = (int)((q.n + KB - 1) / KB);
+    if ((int)(blockIdx.x / count) >= nb || *q.info != 0) return;
+    back_column<B>(q.tiles, q.dinv, q.v, nb, q.words, sh);
+}
+
 }  // namespace
 
 // v (n values, padded to whole tiles) <- L⁻ᵀ v; words: BACK_WORDS doubles of scratch.
@@ -172,6 +199,18 @@ void launch_backward(const double *tiles, const double *dinv, int b, int64_t n, 
     case 256: back_kernel<256><<<nb, 256, 0, s>>>(tiles, dinv, v, nb, w); break;
     case 384: back_kernel<384><<<nb, 256, 0, s>>>(tiles, dinv, v, nb, w); break;
     default: back_kernel<512><<<nb, 256, 0, s>>>(tiles, dinv, v, nb, w); break;
+    }
+}
+
+void launch_backward_batched(int b, const BatchReq *d, int count, int64_t longest, hipStream_t s)
+{
+    back_clear_kernel<<<(unsigned)ceil_div(count, 256), 256, 0, s>>>(d, count);
+    const unsigned grid = (unsigned)(count * ceil_div(longest, KB));
+    switch (b) {
+    case 128: back_batched_kernel<128><<<grid, 256, 0, s>>>(d, count); break;
+    case 256: back_batched_kernel<256><<<grid, 256, 0, s>>>(d, count); break;
+    case 384: back_batched_kernel<384><<<grid, 256, 0, s>>>(d, count); break;
+    default: back_batched_kernel<512><<<grid, 256, 0, s>>>(d, count); break;
     }
 }
 

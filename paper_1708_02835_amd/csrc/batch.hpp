@@ -47,6 +47,9 @@ void launch_gen_batched(int b, const BatchReq *d, int count, int64_t tiles, bool
 // part of builds without device code).
 void launch_flow_batched(int b, const BatchReq *d, int count, int64_t blocks, int64_t pads, hipStream_t s)
     __attribute__((weak));
+// v <- L⁻ᵀ v for every request whose factorisation succeeded, in one launch (back.hip); d as after
+// enqueue_whole (its words are used again), longest: the largest n.
+void launch_backward_batched(int b, const BatchReq *d, int count, int64_t longest, hipStream_t s);
 void launch_final_batched(const BatchReq *d, int count, hipStream_t s);
 
 // The whole evaluations of d[0..count) (count >= 1): staging and Σ generation,

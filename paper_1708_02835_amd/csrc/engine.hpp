@@ -197,6 +197,17 @@ int ind_eval(gl_context *ctx, const double *x, const double *y, const double *z,
 int ind_krige(gl_context *ctx, const double *x, const double *y, const double *z, const int64_t *kcount,
               const double *xnew, const double *ynew, const int64_t *mcount, int64_t nblocks, gl_theta th,
               const gl_opts &o, int b, double *znew, hipStream_t s);
+// Folds f0 .. f1 - 1 of an exact binary64 cross-validation, input order, all at
+// once: every fold's factorisation and backward solve in one launch each, its
+// predictions and MSE as krige_cv returns them (NaN where Σ is not positive
+// definite: GL_NOT_SPD).  count: locations per fold (host); tiles of b for all
+// of them.  GL_ENOMEM, before anything is enqueued, when they do not fit.
+// cv_fold_bytes: workspace of one fold that observes nk of n locations.
+// (weak: not part of builds without device code)
+int cv_folds(gl_context *ctx, const double *x, const double *y, const double *z, int64_t n, gl_theta th,
+             const gl_opts &o, int b, const int32_t *fold_h, const int64_t *count, int32_t f0, int32_t f1, double *mse_h,
+             double *pred_out, hipStream_t s) __attribute__((weak));
+size_t cv_fold_bytes(int64_t n, int64_t nk, int b) __attribute__((weak));
 
 }  // namespace gl
 
