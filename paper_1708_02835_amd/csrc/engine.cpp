@@ -487,12 +487,12 @@ int matern_generate(gl_context *ctx, const double *x1, const double *y1, int64_t
 namespace gl {
 
 // Likelihood evaluation on a prepared workspace whose x, y, v hold the padded
-// inputs.  Leaves the factor and w = L⁻¹ Z in the workspace and enqueues the
-// copy of the scalar results to out_h (pinned host memory).
+// inputs (stage_inputs).  Leaves the factor and w = L⁻¹ Z in the workspace; the
+// last kernel writes the scalar results to out_h (pinned host memory, which the
+// device addresses: no copy behind it).
 int eval_launch(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream_t s, DevResult *out_h,
                 MixedPlan *plan_out)
 {
-    launch_fill(reinterpret_cast<double *>(w.info), 1, 0.0, s);
     int rc;
     if (o.precision == GL_FP64) {
         timed(ln.prof, GL_PHASE_GEN, 0.0, s,
@@ -503,9 +503,8 @@ int eval_launch(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream_t s
     }
     if (rc != GL_OK) return rc;
     timed(o.precision == GL_FP64 ? ln.prof : nullptr, GL_PHASE_REDUCE, 0.0, s,
-          [&] { launch_final_reduce(w.logsum, w.quad, w.nt, w.n, w.info, w.res, s); });
+          [&] { launch_final_reduce(w.logsum, w.quad, w.nt, w.n, w.info, out_h, s); });
     GL_HIP_TRY(hipGetLastError());
-    GL_HIP_TRY(hipMemcpyAsync(out_h, w.res, sizeof(DevResult), hipMemcpyDeviceToHost, s));
     return GL_OK;
 }
 
@@ -531,13 +530,17 @@ bool valid_opts(const gl_opts &o)
 
 void stage_inputs(Work &w, const double *x, const double *y, const double *z, int reorder, hipStream_t s)
 {
-    if (reorder) {
-        launch_morton_order(x, y, z, w.n, w.npad, w.keys, w.x, w.y, w.v, nullptr, s);
-    } else {
+    if (reorder) launch_morton_order(x, y, z, w.n, w.npad, w.keys, w.x, w.y, w.v, nullptr, s);
+    if (launch_stage) {
+        launch_stage(w, reorder ? nullptr : x, y, z, s);
+        return;
+    }
+    if (!reorder) {
         launch_copy_pad(x, w.n, w.x, w.npad, 0.0, s);
         launch_copy_pad(y, w.n, w.y, w.npad, 0.0, s);
         launch_copy_pad(z, w.n, w.v, w.npad, 0.0, s);
     }
+    launch_fill(reinterpret_cast<double *>(w.info), 1, 0.0, s);
 }
 
 // Mode defaults for negative thresholds: FP32 mode keeps every off-band tile
@@ -552,7 +555,7 @@ gl_opts resolved_opts(const gl_opts &in)
 }
 
 // FP64 evaluation through a captured hipGraph of everything after staging:
-// fill, Σ(θ) generation with θ read from device memory, the tiled
+// Σ(θ) generation with θ read from device memory, the tiled
 // factorisation with its lookahead lane, the final reduction.  The graph is
 // captured on the first call for a workspace geometry and distance and
 // replayed afterwards; the staging copies and θ's upload run outside it, on
@@ -581,8 +584,9 @@ static int graph_eval(gl_context *ctx, Work &w, const double *x, const double *y
     *ctx->theta_h = th;  // the previous call synchronised, so the last upload is done
     GL_HIP_TRY(hipMemcpyAsync(ctx->theta_d, ctx->theta_h, sizeof(gl_theta), hipMemcpyHostToDevice, g));
     // The graph holds pointers into the tiles and into the vectors (x, y, v,
-    // the per-tile sums, the diagonal-block inverses, info, result), so any
-    // reallocation of the workspace invalidates it, even when the tiles stay.
+    // the per-tile sums, the diagonal-block inverses, info), so any
+    // reallocation of the workspace invalidates it, even when the tiles stay;
+    // its last kernel writes the context's pinned result.
     const int64_t near = near_tiles_for(w.b, o.near_tiles);
     const bool hit = ctx->gexec && ctx->gkey_gen == w.gen && ctx->gkey_n == w.n && ctx->gkey_b == w.b &&
                      ctx->gkey_geo.metric == geo.metric && ctx->gkey_geo.radius == geo.radius &&
@@ -592,10 +596,9 @@ static int graph_eval(gl_context *ctx, Work &w, const double *x, const double *y
         Lanes ln = ctx->lanes;
         ln.prof = nullptr;  // no timing events inside a graph
         GL_HIP_TRY(hipStreamBeginCapture(g, hipStreamCaptureModeThreadLocal));
-        launch_fill(reinterpret_cast<double *>(w.info), 1, 0.0, g);
         launch_gen_tiles_dev(w.tiles, w.x, w.y, w.n, w.b, w.nt, ctx->theta_d, geo, g);
         int rc = factor_fp64(ln, w, g, true, o.near_tiles);
-        launch_final_reduce(w.logsum, w.quad, w.nt, w.n, w.info, w.res, g);
+        launch_final_reduce(w.logsum, w.quad, w.nt, w.n, w.info, ctx->res_h, g);
         hipGraph_t graph = nullptr;
         const hipError_t ec = hipStreamEndCapture(g, &graph);
         if (rc != GL_OK || ec != hipSuccess) {
@@ -616,7 +619,6 @@ static int graph_eval(gl_context *ctx, Work &w, const double *x, const double *y
         ctx->gkey_near = near;
     }
     GL_HIP_TRY(hipGraphLaunch(ctx->gexec, g));
-    GL_HIP_TRY(hipMemcpyAsync(ctx->res_h, w.res, sizeof(DevResult), hipMemcpyDeviceToHost, g));
     GL_HIP_TRY(hipEventRecord(ctx->gev[1], g));
     GL_HIP_TRY(hipStreamWaitEvent(s, ctx->gev[1], 0));
     GL_HIP_TRY(hipStreamSynchronize(g));
@@ -972,10 +974,7 @@ int synth_generate(gl_context *ctx, const double *x, const double *y, const doub
     Work &w = ctx->ws;
     int rc = w.ensure(ctx, n, pick_tile(n, o.tile), GL_FP64);
     if (rc != GL_OK) return rc;
-    launch_copy_pad(x, n, w.x, w.npad, 0.0, s);
-    launch_copy_pad(y, n, w.y, w.npad, 0.0, s);
-    launch_copy_pad(e, n, w.v, w.npad, 0.0, s);
-    launch_fill(reinterpret_cast<double *>(w.info), 1, 0.0, s);
+    stage_inputs(w, x, y, e, 0, s);
     launch_gen_tiles(w.tiles, w.x, w.y, w.n, w.b, w.nt, th, geom_of(o), nullptr, s);
     rc = factor_fp64(ctx->lanes, w, s, false, o.near_tiles);
     if (rc != GL_OK) return rc;

@@ -147,6 +147,11 @@ int eval_launch(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream_t s
 // Copy n inputs into the padded workspace vectors, in Morton order when
 // `reorder` is set.
 void stage_inputs(Work &w, const double *x, const double *y, const double *z, int reorder, hipStream_t s);
+// The same for inputs in their own order (x null: nothing to copy, after
+// launch_morton_order) in one launch, with info and the progress words of
+// flow_factorize cleared (weak: not part of builds without device code).
+void launch_stage(const Work &w, const double *x, const double *y, const double *z, hipStream_t s)
+    __attribute__((weak));
 gl_opts resolved_opts(const gl_opts &in);
 bool valid_opts(const gl_opts &o);
 bool valid_metric(const gl_opts &o);

@@ -807,12 +807,11 @@ int flow_factorize(Work &w, hipStream_t s, bool solve)
     p.pad = (int)(w.npad / FB) - p.nb;
     p.solve = solve;
     // the words take the place of the sort keys, which the staging is done
-    // with; a cache line each where the keys leave room
+    // with (and clears); a cache line each where the keys leave room
     p.words = reinterpret_cast<int *>(w.keys);
     p.stride = flow_stride(w.n);
     const int64_t bytes = flow_words(w.n, p.stride) * (int64_t)sizeof(int);
     if (bytes > (npow2_of(w.n) + 4) * (int64_t)sizeof(uint64_t)) return GL_EINVAL;
-    launch_fill(reinterpret_cast<double *>(w.keys), ceil_div(bytes, 8), 0.0, s);
     const int64_t tasks = (int64_t)p.nb * (p.nb + 1) / 2 + p.pad;
     const unsigned grid = (unsigned)std::min<int64_t>(tasks, 512);
     switch (w.b) {

@@ -44,7 +44,7 @@ __global__ void ind_total_kernel(const DevResult *__restrict__ r, int64_t nblk, 
 
 // The blocks of one IND factorisation: one descriptor per block (factor
 // tiles, padded coordinates, w = L⁻¹ Z of the block in v), the locations the
-// blocks were cut from (input or Morton order) and the device total.
+// blocks were cut from (input or Morton order) and the per-block results.
 struct IndPlan {
     int b = 0;
     int64_t nblk = 0;
@@ -55,7 +55,6 @@ struct IndPlan {
     const double *sx = nullptr, *sy = nullptr;
     const BatchReq *desc = nullptr;     // device descriptors
     const DevResult *res = nullptr;     // per-block results (device)
-    DevResult *total = nullptr;
 };
 
 static size_t word_doubles(int64_t n) { return (size_t)(flow_words(n, flow_stride(n)) + 1) / 2; }
@@ -72,8 +71,8 @@ static size_t block_doubles(int64_t n, int b)
 }
 
 // The blocks [start[i], start[i] + count[i]) of n locations (each count >= 1)
-// and the layout of their workspace, in doubles: descriptors | total |
-// per-block results, info | per block: its workspace | reordered inputs, keys
+// and the layout of their workspace, in doubles: descriptors | per-block
+// results, info | per block: its workspace | reordered inputs, keys
 static void ind_layout(int b, const std::vector<int64_t> &start, const std::vector<int64_t> &count, int64_t n,
                        bool reorder, IndPlan &p)
 {
@@ -81,7 +80,7 @@ static void ind_layout(int b, const std::vector<int64_t> &start, const std::vect
     p.nblk = (int64_t)start.size();
     p.start = start;
     p.nb = count;
-    size_t off = desc_doubles(p.nblk) + 8 + 16 * (size_t)p.nblk;
+    size_t off = desc_doubles(p.nblk) + 16 * (size_t)p.nblk;
     for (int64_t i = 0; i < p.nblk; ++i) {
         p.off.push_back(off);
         p.ntb.push_back(ceil_div(count[i], b));
@@ -112,7 +111,7 @@ static int ind_workspace(gl_context *ctx, size_t bytes)
 }
 
 // Enqueues the factorisation of the blocks of p (ind_layout) in the workspace
-// `base` and the fixed-order sum of the per-block results into p.total (all
+// `base` and the fixed-order sum of the per-block results into ctx->res_h (all
 // on s).  With reorder the locations are first put in Morton order.  block:
 // uniform block length (the likelihood's), for the reported column.
 static int ind_factor(gl_context *ctx, const double *x, const double *y, const double *z, int64_t n, gl_theta th,
@@ -121,9 +120,8 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
     const int64_t nblk = p.nblk;
     const int b = p.b;
     BatchReq *ddesc = reinterpret_cast<BatchReq *>(base);
-    DevResult *total = reinterpret_cast<DevResult *>(base + desc_doubles(nblk));
-    DevResult *bres = reinterpret_cast<DevResult *>(base + desc_doubles(nblk) + 8);
-    int64_t *binfo = reinterpret_cast<int64_t *>(base + desc_doubles(nblk) + 8 + 8 * nblk);
+    DevResult *bres = reinterpret_cast<DevResult *>(base + desc_doubles(nblk));
+    int64_t *binfo = reinterpret_cast<int64_t *>(base + desc_doubles(nblk) + 8 * nblk);
     const double *sx = x, *sy = y, *sz = z;
     if (reorder) {
         double *xo = base + p.morton, *yo = xo + n, *zo = yo + n;
@@ -180,14 +178,13 @@ static int ind_factor(gl_context *ctx, const double *x, const double *y, const d
     const int rc = enqueue_whole(ctx->ind_host, ddesc, (int)nblk, b, s, nullptr);
     if (rc != GL_OK) return rc;
     GL_HIP_TRY(hipEventRecord(ctx->ind_done, s));
-    ind_total_kernel<<<1, 64, 0, s>>>(bres, nblk, block, total);
+    ind_total_kernel<<<1, 64, 0, s>>>(bres, nblk, block, ctx->res_h);
     GL_HIP_TRY(hipGetLastError());
     p.proto = std::move(proto);
     p.sx = sx;
     p.sy = sy;
     p.desc = ddesc;
     p.res = bres;
-    p.total = total;
     return GL_OK;
 }
 
@@ -207,7 +204,6 @@ int ind_eval(gl_context *ctx, const double *x, const double *y, const double *z,
     if (rc == GL_OK)
         rc = ind_factor(ctx, x, y, z, n, th, o, block, o.reorder != 0, static_cast<double *>(ctx->ind_buf), s, p);
     if (rc != GL_OK) return res->status = rc;
-    GL_HIP_TRY(hipMemcpyAsync(ctx->res_h, p.total, sizeof(DevResult), hipMemcpyDeviceToHost, s));
     GL_HIP_TRY(hipStreamSynchronize(s));
     fill_result(res, *ctx->res_h, p.b);
     return res->status;
@@ -237,7 +233,6 @@ int ind_krige(gl_context *ctx, const double *x, const double *y, const double *z
             rc = ind_factor(ctx, x, y, z, n, th, o, o.ind_tiles * (int64_t)b, false,
                             static_cast<double *>(ctx->ind_buf), s, p);
         if (rc != GL_OK) return rc;
-        GL_HIP_TRY(hipMemcpyAsync(ctx->res_h, p.total, sizeof(DevResult), hipMemcpyDeviceToHost, s));
         GL_HIP_TRY(hipStreamSynchronize(s));
         if (ctx->res_h->info != 0) return GL_NOT_SPD;
         // X = L⁻ᵀ w within each block, in place
@@ -274,7 +269,7 @@ size_t cv_fold_bytes(int64_t n, int64_t nk, int b)
     const int64_t nm = n - nk;
     // index list, known x, y, z | missing x, y, z, prediction, kriging sums | mse, result
     const size_t own = n + 3 * nk + (4 + krige_chunks(nk)) * (size_t)nm + 1 + 8;
-    return (block_doubles(nk, b) + desc_doubles(1) + 24 + own) * sizeof(double);
+    return (block_doubles(nk, b) + desc_doubles(1) + 16 + own) * sizeof(double);
 }
 
 int cv_folds(gl_context *ctx, const double *x, const double *y, const double *z, int64_t n, gl_theta th,
