@@ -885,10 +885,16 @@ int mixed_factorize(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream
     if (rc != GL_OK) return rc;
     if (plan_out) *plan_out = plan;
     // Every tile binary64 (the thresholds found no tile whose class error
-    // stays within the accuracy target): the binary64 schedule, with its
-    // two-panel passes, continues after the POTRF of tile 0 done above.
+    // stays within the accuracy target): the binary64 factorisation, in one
+    // launch from a freshly generated tile 0, or
+    // by steps, which continue after the POTRF of tile 0 done above.
+    // BF16 mode, every tile binary64: n = 8,100 5.6 ms (10.2 by steps), n = 40,000 334 (370).
     bool all64 = true;
     for (int c = 1; c < NCLASS; ++c) all64 = all64 && plan.tiles[c] == 0;
+    if (all64 && flow_factorize && !ln.prof && o.near_tiles == 0) {
+        launch_gen_tiles(w.tiles, w.x, w.y, std::min<int64_t>(w.n, w.b), w.b, 1, th, geom_of(o), nullptr, s);
+        return flow_factorize(w, s, true);
+    }
     if (all64) return factorize(ln, w, s, true, near_tiles_for(w.b, o.near_tiles), true);
     hipStream_t la = ln.la;
     const bool pairs = w.precision == GL_MIXED_BF16 || w.precision == GL_MIXED_FP16;

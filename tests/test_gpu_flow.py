@@ -84,3 +84,22 @@ def test_flow_reports_the_failing_column(g, ctx, first, tile):
     xs, ys = geoinputs.jittered_grid(n, 7)
     a, b = both(g, ctx, dev(xs), dev(ys), dev(z), tile=tile)
     assert a["status"] == g.GL_OK and a["loglik"] == b["loglik"]
+
+
+@pytest.mark.parametrize("n,tile,bad", [(100, 128, None), (129, 128, None), (900, 256, None), (1300, 512, None),
+                                        (900, 256, 40), (900, 256, 700)])
+@pytest.mark.parametrize("prec", [1, 3])
+def test_mixed_call_that_stays_binary64_takes_one_launch(g, ctx, prec, n, tile, bad):
+    """tol_64 = 0 keeps every tile binary64; tile 0, factored for the thresholds,
+    is generated again: the bits of GL_FP64 in Morton order, and its failing
+    column where a location is repeated (in the first tile or a later one)."""
+    x, y = geoinputs.jittered_grid(n, 6)
+    z = geoinputs.normal_vector(n, 6)
+    if bad is not None:
+        x[bad + 1], y[bad + 1] = x[bad], y[bad]
+    xd, yd, zd = dev(x), dev(y), dev(z)
+    a = g.loglik_eval(ctx, xd, yd, zd, THETA, g.gl_opts_default(precision=prec, tile=tile, tol_64=0.0))
+    b = g.loglik_eval(ctx, xd, yd, zd, THETA, g.gl_opts_default(tile=tile, reorder=1))
+    assert (a["status"], a["info"]) == (b["status"], b["info"])
+    if b["status"] == g.GL_OK:
+        assert (a["loglik"], a["logdet"], a["quad"]) == (b["loglik"], b["logdet"], b["quad"])
