@@ -120,6 +120,8 @@ typedef struct {
                             workspace geometry (n, tile) and distance and replayed while they
                             stay the same (θ is read from device memory); 0: direct launches */
     int32_t near_tiles;  /* schedule of the trailing updates (results change by rounding only).
+                            0: GL_FP64 factorises in one launch, which has no such schedule;
+                            > 0 asks for a launch per tile step.  Then, and in the mixed modes:
                             GL_FP64 and the split-product classes of the mixed modes apply two
                             panels per pass (K = 2b) to the columns beyond the nearest ones: at
                             an even step k the next column and the nearest columns holding about
@@ -407,7 +409,9 @@ int gl_precision_stats(gl_context *ctx, int64_t *tiles_h, double *work_h, double
  * 3 = FP16 16x16x32. */
 int gl_selftest(gl_context *ctx, int32_t which, double *out_h, int64_t cap);
 
-/* Kernel timing by phase of Alg. 2.  While enabled, kernel launches of the
+/* Kernel timing by phase of Alg. 2.  While enabled, GL_FP64 calls factorise
+ * with a launch per tile step and phase (the same results; otherwise the whole
+ * factorisation is one launch, which has no phases to time), and kernel launches of the
  * direct calls are bracketed by HIP events on the stream they run on: on = 1
  * the trailing updates only (the dominant kernel family), on = 2 every phase
  * below; 0 switches timing off.  In the mixed-precision modes only the

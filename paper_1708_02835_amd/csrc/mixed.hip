@@ -886,9 +886,9 @@ int mixed_factorize(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream
     if (plan_out) *plan_out = plan;
     // Every tile binary64 (the thresholds found no tile whose class error
     // stays within the accuracy target): the binary64 factorisation, in one
-    // launch from a freshly generated tile 0, or
-    // by steps, which continue after the POTRF of tile 0 done above.
-    // BF16 mode, every tile binary64: n = 8,100 5.6 ms (10.2 by steps), n = 40,000 334 (370).
+    // launch from a freshly generated tile 0, or by steps, which continue
+    // after the POTRF of tile 0 done above.  Measured in the BF16 mode:
+    // n = 8,100 5.6 ms (by steps 10.2), n = 40,000 334 ms (370).
     bool all64 = true;
     for (int c = 1; c < NCLASS; ++c) all64 = all64 && plan.tiles[c] == 0;
     if (all64 && flow_factorize && !ln.prof && o.near_tiles == 0) {

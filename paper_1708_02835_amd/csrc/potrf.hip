@@ -3,11 +3,9 @@
 //
 // One workgroup of 256 threads factors the b×b tile A_kk = L_kk L_kkᵀ in place
 // (lower triangle), right-looking over 64-column panels s:
-//   1. the 64×64 diagonal block D is copied to LDS, factored and inverted in
-//      16×16 sub-blocks (factor_invert_64: small scalar factorisations and
-//      inverses of the diagonal sub-blocks, everything else on the matrix
-//      cores).  D⁻¹ is also written to `dinv` for the panel TRSM and the
-//      forward solve of this step;
+//   1. the 64×64 diagonal block D is copied to LDS, factored and inverted by
+//      16-column panels (factor_invert_64).  D⁻¹ is also written to `dinv`
+//      for the panel TRSM and the forward solve of this step;
 //   2. the rows below the block are solved on the matrix cores as
 //      P = A[s+64:, s:s+64] · D⁻ᵀ, each wave owning whole 16-row groups;
 //   3. the trailing lower triangle A[s+64:, s+64:] -= P Pᵀ is updated on the
