@@ -26,7 +26,7 @@
 // coherence point (agent-scope stores), the word follows once those stores are
 // acknowledged, and a reader invalidates its caches after it has seen the word.
 // A pivot that is not positive stores its column in *info; workgroups that
-// wait see it and leave.
+// wait see it and leave the task (and the launch, if it has no other problem).
 //
 // The chain is diagonal block j -> block (j + 1, j) -> the last panel of
 // diagonal block j + 1, with block (j + 2, j), which block (j + 2, j + 1) needs,
@@ -708,7 +708,9 @@ __global__ __launch_bounds__(256, 2) void flow_batched_kernel(const BatchReq *__
         const int c = flow_column(u / active, (int)((last.n + FB - 1) / FB), below);
         const FlowProb p = flow_prob(d[u % active], B / FB);
         const int j = c + p.nb - (int)((last.n + FB - 1) / FB);
-        if (!flow_task<B>(p, j + below, j, sh)) return;
+        // a block of a failed factorisation is left where it meets a word that
+        // will not come; the other problems' blocks still want this workgroup
+        (void)flow_task<B>(p, j + below, j, sh);
     }
 }
 
