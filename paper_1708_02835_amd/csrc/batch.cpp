@@ -11,6 +11,7 @@ int enqueue_whole(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, i
 {
     std::sort(d, d + count, [](const BatchReq &x, const BatchReq &y) { return x.n > y.n; });
     int64_t o_stage = 0, o_gen = 0, o_flow = 0, pads = 0;
+    double flops = 0.0;
     bool euclid = true;
     for (int i = 0; i < count; ++i) {
         BatchReq &q = d[i];
@@ -25,6 +26,7 @@ int enqueue_whole(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, i
         // columns with nb .. next + 1 blocks left, in i + 1 factorisations each
         o_flow += (i + 1) * (tile_count(nb) - tile_count(next));
         pads += q.npad / 128 - nb;
+        flops += (double)q.n * q.n * q.n / 3.0;
         euclid = euclid && q.geo.metric == GL_EUCLIDEAN;
     }
     if (o_flow + pads > INT32_MAX) return GL_EINVAL;
@@ -32,7 +34,7 @@ int enqueue_whole(BatchReq *d, BatchReq *dev, int count, int b, hipStream_t s, i
     launch_stage_batched(dev, count, o_stage, s);
     launch_gen_batched(b, dev, count, o_gen, euclid, s);
     if (launch_flow_batched) {
-        launch_flow_batched(b, dev, count, o_flow, pads, s);
+        launch_flow_batched(b, dev, count, o_flow, pads, flops, s);
     } else {
         for (int i = 0; i < count; ++i) {
             const BatchReq &q = d[i];

@@ -51,9 +51,9 @@ void launch_stage_batched(const BatchReq *d, int count, int64_t blocks, hipStrea
 // euclid: every request that generates in this launch uses the Euclidean distance.
 void launch_gen_batched(int b, const BatchReq *d, int count, int64_t tiles, bool euclid, hipStream_t s);
 // Factorisations and forward solves of all requests, sorted by falling size:
-// `blocks` 128×128 blocks in all and `pads` all-padding diagonal blocks (flow.hip; weak: not
-// part of builds without device code).
-void launch_flow_batched(int b, const BatchReq *d, int count, int64_t blocks, int64_t pads, hipStream_t s)
+// `blocks` 128×128 blocks in all, `pads` all-padding diagonal blocks and `flops`, the sum of
+// n³/3 (flow.hip; weak: not part of builds without device code).
+void launch_flow_batched(int b, const BatchReq *d, int count, int64_t blocks, int64_t pads, double flops, hipStream_t s)
     __attribute__((weak));
 // v <- L⁻ᵀ v for every request whose factorisation succeeded, in one launch (back.hip); d as after
 // enqueue_whole (its words are used again), longest: the largest n.

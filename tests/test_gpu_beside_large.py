@@ -1,0 +1,88 @@
+"""Work beside a large factorisation gets onto the chip while it runs: a small
+request of the queue beside a large one on a stream of its own, and a kernel of
+another stream beside a direct call.  Each arrives in the first tenth of the
+large evaluation and has to be done in less than half of its time (alone it
+takes less than a hundredth of it; kept out, it waits for nearly all of it)."""
+import threading
+import time
+
+import numpy as np
+import pytest
+
+import geoinputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+THETA = (1.0, 0.1, 0.5)
+LARGE = 40000
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_1708_02835_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+@pytest.fixture(scope="module")
+def ctx(g):
+    c = g.Context(0)
+    yield c
+    c.close()
+
+
+def field(n, seed):
+    return [torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+            for a in (*geoinputs.jittered_grid(n, seed), geoinputs.normal_vector(n, seed))]
+
+
+def test_small_request_beside_a_large_one(g, ctx):
+    sets = [g.gl_dataset_register(ctx, *field(n, 51)) for n in (LARGE, 1000)]
+    q = g.lq_create(ctx)
+    try:
+        for s in sets:  # workspaces and streams exist from here on
+            assert g.lq_wait(q, g.lq_submit(q, s, THETA), int(60e6))["status"] == g.GL_OK
+        t0 = time.perf_counter()
+        large = g.lq_submit(q, sets[0], THETA)
+        time.sleep(0.02)
+        t1 = time.perf_counter()
+        assert g.lq_wait(q, g.lq_submit(q, sets[1], THETA), int(60e6))["status"] == g.GL_OK
+        t2 = time.perf_counter()
+        assert g.lq_wait(q, large, int(60e6))["status"] == g.GL_OK
+        t3 = time.perf_counter()
+        print(f"small {t2 - t1:.4f} s, large {t3 - t0:.4f} s", flush=True)
+        assert t2 - t1 < 0.5 * (t3 - t0)
+    finally:
+        g.lq_destroy(q)
+        for s in sets:
+            g.gl_dataset_release(ctx, s)
+
+
+def test_kernel_of_another_stream_runs_beside_a_large_evaluation(g, ctx):
+    x, y, z = field(LARGE, 52)
+    a = torch.ones(1 << 20, device="cuda")
+    side = torch.cuda.Stream()
+    g.loglik_eval(ctx, x, y, z, THETA)
+    with torch.cuda.stream(side):
+        b = a * 2
+    torch.cuda.synchronize()
+    took = []
+
+    def evaluate():
+        t0 = time.perf_counter()
+        g.loglik_eval(ctx, x, y, z, THETA)
+        took.append(time.perf_counter() - t0)
+
+    th = threading.Thread(target=evaluate)
+    th.start()
+    time.sleep(0.02)
+    t1 = time.perf_counter()
+    with torch.cuda.stream(side):
+        b = a * 3
+    side.synchronize()
+    t2 = time.perf_counter()
+    th.join()
+    print(f"kernel {t2 - t1:.4f} s, evaluation {took[0]:.4f} s", flush=True)
+    assert float(b[0]) == 3.0
+    assert t2 - t1 < 0.5 * took[0]
