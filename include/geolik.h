@@ -327,12 +327,14 @@ int gl_dataset_release(gl_context *ctx, uint64_t ds);
 typedef struct {
     int32_t max_inflight;    /* requests resident on the device at once (1..64) */
     int32_t streams;         /* requests run one at a time per stream outside the fused
-                                launches; this many such streams (1..8), each created
-                                when its first request arrives (the fused launches use
-                                two streams of their own) */
+                                launches; this many such streams (1..8; the fused launches
+                                use two of their own), side by side as far as the
+                                process' hardware queues (four by default) are enough */
     int32_t batch_small;     /* 1: FP64 requests with n <= small_n (tile 0 or 256, no
                                 reordering) run together in fused launches, the whole
-                                evaluations of a batch per launch, tile 256 */
+                                evaluations of a batch per launch, tile 256; a launch
+                                takes requests up to a bound of work (8 Tflop), those with
+                                n <= 4,096 in launches of their own */
     int32_t small_n;         /* size limit of the fused path */
     size_t hbm_budget_bytes; /* admission budget for resident work (0 = the context's) */
 } lq_config;
@@ -366,8 +368,9 @@ int lq_poll(lq_queue *q, uint64_t ticket, gl_result *res_h);
  * the request's status; a delivered result retires the ticket. */
 int lq_wait(lq_queue *q, uint64_t ticket, gl_result *res_h, int64_t timeout_us);
 
-/* Cancel a request that has not started on the device. GL_OK if cancelled,
- * GL_EBUSY if it is already running or done. */
+/* Cancel a request that has not started on the device (also one that is admitted
+ * and waits for the next launch). GL_OK if cancelled, GL_EBUSY if it is already
+ * running or done. */
 int lq_cancel(lq_queue *q, uint64_t ticket);
 
 /* Counters since creation: completed requests, peak resident bytes, peak

@@ -4,15 +4,15 @@
 // A scheduler thread serves requests in two ways.
 //
 // Batching (FP64 requests with n <= small_n): admitted requests join a
-// resident set; a scheduler tick enqueues the whole evaluations of a cohort's
-// residents in fused launches (staging, Σ generation, all factorisations and
+// resident set; a scheduler tick enqueues the whole evaluations of residents of
+// a cohort in fused launches (staging, Σ generation, all factorisations and
 // forward solves in one launch, final reductions; see enqueue_whole).
-// Requests that arrive meanwhile join the next tick.  Residents are spread
-// over two cohorts with their own streams, so one cohort's tail (few blocks
-// left, bound by its chain) runs beside the other's bulk; each cohort may have
-// two ticks in flight.  Each request runs the same per-request code as a single
-// evaluation with tile 256, so its result does not depend on the batch it
-// rides in.
+// Requests that arrive meanwhile join the next tick.  A result and a workspace
+// are held until their tick ends, so a tick takes residents up to a bound of
+// work (TICK_FLOPS), and short requests (n <= TICK_SHORT) have a cohort of their
+// own.  Each cohort has a stream and may have two ticks in flight.  Each request
+// runs the same per-request code as a single evaluation with tile 256, so its
+// result does not depend on the batch it rides in.
 //
 // Other requests use device slots (a stream, a lookahead lane, a workspace
 // and a pinned result buffer each) and run their whole evaluation on the
@@ -121,10 +121,19 @@ constexpr int TICK_B = 256;     // tile size of the batched engine
 constexpr int TICK_RING = 4;    // descriptor buffers
 constexpr int TICK_DEPTH = 2;   // ticks in flight
 constexpr int TICK_MAX = 64;    // residents per tick
+// Work of a tick beyond one request: that of five of n = 16,500, about 110 ms, a
+// result's and a workspace's longest stay.  TICK_SHORT: up to here one request
+// leaves most of the chip idle.  A request of 1,000 points with 15 of 16,000 takes
+// 1.1 ms (170 to 320 in their ticks); 64 optimisers on 1,000 to 16,000 points are
+// served 164 evaluations/s, median latency 379 ms (159 and 411 with everything in
+// common ticks; 165, 388 and a shorter tail with 6e12).
+constexpr double TICK_FLOPS = 8e12;
+constexpr int64_t TICK_SHORT = 4096;
 
 struct Resident {
     Request *req = nullptr;
     Work *w = nullptr;
+    double flops = 0.0;
 };
 
 struct TickBuf {
@@ -137,14 +146,13 @@ struct TickBuf {
     std::vector<Resident> finishing;
 };
 
-// Residents are split into cohorts that tick independently on their own
-// streams, so one cohort's short, narrow launches (POTRF, TRSM, solves)
-// overlap another cohort's wide trailing update.
-constexpr int NCOHORT = 2;
+// Cohorts tick independently on their own streams: short requests, and the others
+// (two cohorts of those, whose workgroups the chip would mix, take 3 % longer).
+enum { LONG = 0, SHORT = 1, NCOHORT = 2 };
 
 struct Cohort {
     hipStream_t s = nullptr;
-    std::vector<Resident> residents;
+    std::vector<Resident> residents;  // not launched yet, in order of arrival
     TickBuf ring[TICK_RING];
     int ring_next = 0;
     std::deque<int> ticks;  // ring indices in flight, oldest first
@@ -274,12 +282,16 @@ bool make_room(lq_queue *q, size_t need, size_t mine, const Slot *keep_slot)
     return held_bytes(q) - mine + need <= q->budget;
 }
 
-// Enqueue one tick of cohort c: the whole evaluations of its residents.
-int build_tick(lq_queue *q, Cohort &co)
+// Enqueue one tick of cohort co: the whole evaluations of its first `count` residents.
+int build_tick(lq_queue *q, Cohort &co, int &count)
 {
     TickBuf &tb = co.ring[co.ring_next];
     if (tb.busy) return GL_EBUSY;
-    const int count = (int)co.residents.size();
+    count = 0;
+    for (double f = 0.0; count < (int)co.residents.size() && count < TICK_MAX; ++count) {
+        f += co.residents[count].flops;
+        if (count > 0 && f > TICK_FLOPS) break;
+    }
     for (int i = 0; i < count; ++i) {
         Resident &r = co.residents[i];
         Work &w = *r.w;
@@ -314,13 +326,11 @@ int build_tick(lq_queue *q, Cohort &co)
     if (rc != GL_OK) return rc;
     tb.finishing.clear();
     GL_HIP_TRY(hipGetLastError());
-    for (const Resident &r : co.residents) {
-        GL_HIP_TRY(hipMemcpyAsync(&tb.res_h[tb.finishing.size()], r.w->res, sizeof(DevResult), hipMemcpyDeviceToHost,
-                                  s));
-        tb.finishing.push_back(r);
-    }
-    co.residents.clear();
+    for (int i = 0; i < count; ++i)
+        GL_HIP_TRY(hipMemcpyAsync(&tb.res_h[i], co.residents[i].w->res, sizeof(DevResult), hipMemcpyDeviceToHost, s));
     GL_HIP_TRY(hipEventRecord(tb.done, s));
+    tb.finishing.assign(co.residents.begin(), co.residents.begin() + count);
+    co.residents.erase(co.residents.begin(), co.residents.begin() + count);
     tb.busy = true;
     co.ticks.push_back(co.ring_next);
     co.ring_next = (co.ring_next + 1) % TICK_RING;
@@ -373,25 +383,45 @@ void retire_ticks(lq_queue *q, Cohort &co)
 }
 
 
-// A slot's stream, its lane (lookahead and forward-solve streams), event and
-// pinned result are created on its first request.  The usual serving load (binary64, n <= small_n) runs
-// through the fused launches on the two cohort streams only, so a queue adds
-// two streams to the process, within the four hardware queues a process gets
-// by default, and the cohorts do not share a hardware queue with idle slots.
-static int slot_open(Slot &sl)
+// Streams of the cohorts and of the first two slots, on hardware queues of their
+// own as far as one can choose: a process gets four by default, and the runtime
+// gives a new stream the one with the fewest streams, of equals possibly the one
+// just taken.  So two streams made first even the counts out, and the four after
+// them, made in turn, differ unless the counts were three apart.  (A short request
+// whose stream shares the long ones' queue waits for their tick.)
+static bool queue_streams(lq_queue *q)
 {
-    if (sl.s) return GL_OK;
-    GL_HIP_TRY(hipStreamCreateWithFlags(&sl.s, hipStreamNonBlocking));
-    if (sl.ln.create() != GL_OK) return GL_EHIP;
-    GL_HIP_TRY(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
-    GL_HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&sl.res_h), sizeof(DevResult), hipHostMallocDefault));
+    hipStream_t *keep[] = {&q->co[LONG].s, &q->co[SHORT].s, &q->slots[0].s, q->slots.size() > 1 ? &q->slots[1].s : nullptr};
+    hipStream_t first[2] = {};
+    bool ok = true;
+    for (hipStream_t &s : first) ok = ok && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;
+    for (hipStream_t *s : keep) ok = ok && (!s || hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess);
+    for (hipStream_t s : first)
+        if (s) (void)hipStreamDestroy(s);
+    return ok;
+}
+
+// A slot's event and pinned result (from the third slot on its stream, too) are
+// created on its first request, its lane (lookahead and forward-solve streams) on
+// the first one that is factored by steps.
+static int slot_open(Slot &sl, const gl_opts &o)
+{
+    if (!sl.s) GL_HIP_TRY(hipStreamCreateWithFlags(&sl.s, hipStreamNonBlocking));
+    if (!sl.done) GL_HIP_TRY(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
+    if (!sl.res_h)
+        GL_HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&sl.res_h), sizeof(DevResult), hipHostMallocDefault));
+    const bool steps = o.precision != GL_FP64 || o.near_tiles > 0 || !flow_factorize;
+    if (steps && !sl.ln.solved) {  // the last one that create() makes
+        sl.ln.destroy();
+        if (sl.ln.create() != GL_OK) return GL_EHIP;
+    }
     return GL_OK;
 }
 
 // Launch request r on slot sl (queue lock released by the caller).
 int launch_on_slot(gl_context *ctx, Slot &sl, Request *r)
 {
-    int rc0 = slot_open(sl);
+    int rc0 = slot_open(sl, r->o);
     if (rc0 != GL_OK) return rc0;
     const int64_t n = r->ds->n;
     const int b = pick_tile(n, r->o.tile);
@@ -437,9 +467,7 @@ void scheduler(lq_queue *q)
         while (!q->queue.empty()) {
             Request *head = q->queue.front();
             if (batch_eligible(q, head)) {
-                Cohort *dst = &q->co[0];
-                for (Cohort &c : q->co)
-                    if (c.residents.size() < dst->residents.size()) dst = &c;
+                Cohort *dst = &q->co[head->ds->n <= TICK_SHORT ? SHORT : LONG];
                 if (q->inflight >= q->cfg.max_inflight || (int)dst->residents.size() >= TICK_MAX) break;
                 const size_t need = work_bytes(head->ds->n, TICK_B, GL_FP64);
                 bool have = false;
@@ -461,6 +489,7 @@ void scheduler(lq_queue *q)
                 Resident res;
                 res.req = head;
                 res.w = w;
+                res.flops = (double)w->n * w->n * w->n / 3.0;
                 dst->residents.push_back(res);
                 ++q->inflight;
                 if (q->inflight > q->peak_inflight) q->peak_inflight = q->inflight;
@@ -504,14 +533,16 @@ void scheduler(lq_queue *q)
         bool ticked = false;
         for (Cohort &c : q->co) {
             if (c.residents.empty() || (int)c.ticks.size() >= TICK_DEPTH) continue;
-            const int rc = build_tick(q, c);
+            int count = 0;
+            const int rc = build_tick(q, c, count);
             if (rc != GL_OK && rc != GL_EBUSY) {
-                for (Resident &r : c.residents) {
+                for (int i = 0; i < count; ++i) {
+                    Resident &r = c.residents[i];
                     --q->inflight;
                     finish(q, r.req, rc);
                     q->pool.push_back(r.w);
                 }
-                c.residents.clear();
+                c.residents.erase(c.residents.begin(), c.residents.begin() + count);
             }
             ticked = ticked || rc == GL_OK;
         }
@@ -624,9 +655,9 @@ int lq_create(gl_context *ctx, const lq_config *cfg, lq_queue **out)
     q->ctx = ctx;
     q->cfg = c;
     q->budget = c.hbm_budget_bytes ? c.hbm_budget_bytes : ctx->budget;
-    q->slots.resize(c.streams);  // their streams are created on first use (slot_open)
+    q->slots.resize(c.streams);
+    bool ok = queue_streams(q);
     for (Cohort &c : q->co) {
-        bool ok = hipStreamCreateWithFlags(&c.s, hipStreamNonBlocking) == hipSuccess;
         for (TickBuf &tb : c.ring)
             ok = ok &&
                  hipHostMalloc(reinterpret_cast<void **>(&tb.host), TICK_MAX * sizeof(BatchReq),
@@ -733,6 +764,18 @@ int lq_cancel(lq_queue *q, uint64_t ticket)
     auto it = q->reqs.find(ticket);
     if (it == q->reqs.end()) return GL_EINVAL;
     Request *r = it->second;
+    if (r->state == RUNNING) {
+        // admitted, but in no tick yet
+        for (Cohort &c : q->co)
+            for (auto ri = c.residents.begin(); ri != c.residents.end(); ++ri)
+                if (ri->req == r) {
+                    q->pool.push_back(ri->w);
+                    c.residents.erase(ri);
+                    --q->inflight;
+                    finish(q, r, GL_ECANCELED);
+                    return GL_OK;
+                }
+    }
     if (r->state != QUEUED) return GL_EBUSY;
     for (auto qi = q->queue.begin(); qi != q->queue.end(); ++qi)
         if (*qi == r) {

@@ -1,8 +1,8 @@
 """Work beside a large factorisation gets onto the chip while it runs: a small
-request of the queue beside a large one on a stream of its own, and a kernel of
-another stream beside a direct call.  Each arrives in the first tenth of the
-large evaluation and has to be done in less than half of its time (alone it
-takes less than a hundredth of it; kept out, it waits for nearly all of it)."""
+request of the queue beside a large one on a stream of its own or beside a batch
+of large ones, and a kernel of another stream beside a direct call.  Each arrives in the first tenth of the
+large work and has to be done in less than half (a third) of its time: alone it
+takes less than a hundredth of it, kept out it waits for nearly all of it."""
 import threading
 import time
 
@@ -57,6 +57,35 @@ def test_small_request_beside_a_large_one(g, ctx):
         g.lq_destroy(q)
         for s in sets:
             g.gl_dataset_release(ctx, s)
+
+
+@pytest.mark.parametrize("delay", [0.0, 0.03])
+def test_small_request_beside_a_batch_of_large_ones(g, ctx, delay):
+    """Submitted with them, or while they run."""
+    sets = [g.gl_dataset_register(ctx, *field(n, 53)) for n in (14000, 1000)]
+    q = g.lq_create(ctx)
+
+    def batch():
+        t0 = time.perf_counter()
+        large = [g.lq_submit(q, sets[0], THETA) for _ in range(16)]
+        time.sleep(delay)
+        t1 = time.perf_counter()
+        small = g.lq_wait(q, g.lq_submit(q, sets[1], THETA), int(60e6))
+        t2 = time.perf_counter()
+        res = [g.lq_wait(q, t, int(60e6)) for t in large]
+        return t2 - t1, time.perf_counter() - t0, [small] + res
+
+    try:
+        batch()  # workspaces exist from here on
+        small, all_of_them, res = batch()
+    finally:
+        g.lq_destroy(q)
+        for s in sets:
+            g.gl_dataset_release(ctx, s)
+    print(f"small {small:.4f} s, batch {all_of_them:.4f} s", flush=True)
+    assert all(r["status"] == g.GL_OK for r in res)
+    assert len({r["loglik"] for r in res[1:]}) == 1
+    assert small < 0.3 * all_of_them
 
 
 def test_kernel_of_another_stream_runs_beside_a_large_evaluation(g, ctx):
