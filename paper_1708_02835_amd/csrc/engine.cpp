@@ -590,11 +590,11 @@ static int graph_eval(gl_context *ctx, Work &w, const double *x, const double *y
     // The graph holds pointers into the tiles and into the vectors (x, y, v,
     // the per-tile sums, the diagonal-block inverses, info), so any
     // reallocation of the workspace invalidates it, even when the tiles stay;
-    // its last kernel writes the context's pinned result.
-    const int64_t near = near_tiles_for(w.b, o.near_tiles);
+    // its last kernel writes the context's pinned result.  near_tiles also
+    // selects the schedule (factor_fp64), so the requested value is the key.
     const bool hit = ctx->gexec && ctx->gkey_gen == w.gen && ctx->gkey_n == w.n && ctx->gkey_b == w.b &&
                      ctx->gkey_geo.metric == geo.metric && ctx->gkey_geo.radius == geo.radius &&
-                     ctx->gkey_near == near;
+                     ctx->gkey_near == o.near_tiles;
     if (!hit) {
         graph_drop(ctx);
         Lanes ln = ctx->lanes;
@@ -620,7 +620,7 @@ static int graph_eval(gl_context *ctx, Work &w, const double *x, const double *y
         ctx->gkey_n = w.n;
         ctx->gkey_b = w.b;
         ctx->gkey_geo = geo;
-        ctx->gkey_near = near;
+        ctx->gkey_near = o.near_tiles;
     }
     GL_HIP_TRY(hipGraphLaunch(ctx->gexec, g));
     GL_HIP_TRY(hipEventRecord(ctx->gev[1], g));

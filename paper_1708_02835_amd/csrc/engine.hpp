@@ -258,7 +258,7 @@ struct gl_context {
     int64_t gkey_n = 0;
     int gkey_b = 0;
     gl::Geom gkey_geo{0, 0.0};
-    int64_t gkey_near = 0;
+    int64_t gkey_near = 0;  // gl_opts.near_tiles
     gl_theta *theta_h = nullptr;  // pinned
     gl_theta *theta_d = nullptr;  // device
     void *scratch = nullptr;      // this device's static workspace of loglik_eval_noalloc
