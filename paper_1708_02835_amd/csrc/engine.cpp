@@ -809,6 +809,7 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     if (!ctx || !f || !xnew || !ynew || !znew || m < 1) return GL_EINVAL;
     FactorUse use(ctx, f);
     if (use.status != GL_OK) return use.status;
+    if (var && !launch_flow_rhs) return GL_EHIP;  // a build without device code
     GL_HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
     Work &w = f->w;
@@ -817,7 +818,7 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     const int64_t nchunk = krige_chunks(w.n);
     const int64_t chunks = var ? std::min<int64_t>(8, ceil_div(m, w.b)) : 0;
     const size_t st_len = (size_t)chunks * w.npad * w.b;
-    const size_t var_len = var && flow_rhs_scratch ? flow_rhs_scratch(w.n, std::min<int64_t>(m, chunks * w.b)) : 0;
+    const size_t var_len = var ? flow_rhs_scratch(w.n, std::min<int64_t>(m, chunks * w.b)) : 0;
     const size_t bytes = (BACK_WORDS + (size_t)w.npad + m * nchunk + 1 + st_len + var_len) * sizeof(double);
     double *scratch = nullptr;
     if (hipMallocAsync(reinterpret_cast<void **>(&scratch), bytes, s) != hipSuccess) {
@@ -827,7 +828,7 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     double *xv = scratch + BACK_WORDS;
     double *part = xv + w.npad;
     double *st = part + m * nchunk + ((m * nchunk) & 1);
-    // X = L⁻ᵀ w
+    // X = L⁻ᵀ w (builds without device code have stand-ins that need no solve)
     launch_copy_pad(w.v, w.npad, xv, w.npad, 0.0, s);
     if (launch_backward) launch_backward(w.tiles, w.dinv, w.b, w.n, xv, scratch, s);
     launch_krige(w.x, w.y, w.n, xv, f->theta, geo, xnew, ynew, m, part, nchunk, s);
@@ -836,8 +837,7 @@ int krige_predict(gl_context *ctx, gl_factor *f, const double *xnew, const doubl
     for (int64_t k0 = 0; var && k0 < m; k0 += chunks * w.b) {
         const int64_t mg = std::min<int64_t>(m - k0, chunks * w.b);
         launch_gen_rhs(st, w.x, w.y, w.n, w.b, w.nt, xnew + k0, ynew + k0, mg, ceil_div(mg, w.b), f->theta, geo, s);
-        if (launch_flow_rhs)
-            launch_flow_rhs(w, st, mg, f->theta.theta1, st + st_len, var + k0, s);
+        launch_flow_rhs(w, st, mg, f->theta.theta1, st + st_len, var + k0, s);
     }
     GL_HIP_TRY(hipGetLastError());
     GL_HIP_TRY(hipFreeAsync(scratch, s));
