@@ -166,7 +166,9 @@ __device__ __forceinline__ int thread_index()
 }
 
 // 64×64 column-major block (ld) to LDS, column m's row c at m·64 + (c ^ 16 (m & 1)):
-// the two 16-lane halves of an operand read fall in different banks.
+// the two 16-lane halves of an operand read fall in different banks.  src is as
+// its doubles are, 8-byte aligned: a workspace's dinv follows nt (nt + 1) / 2 norms.
+typedef double d2_any __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ void stage64(const double *__restrict__ src, int64_t ld, double *dst)
 {
     const int tid = thread_index();
@@ -174,7 +176,7 @@ __device__ __forceinline__ void stage64(const double *__restrict__ src, int64_t 
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int e = 2 * tid + 512 * q;
-        r[q] = *reinterpret_cast<const d2 *>(src + (e >> 6) * ld + (e & 63));
+        r[q] = *reinterpret_cast<const d2_any *>(src + (e >> 6) * ld + (e & 63));
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
