@@ -75,6 +75,7 @@ constexpr int FB = 128;      // block edge
 constexpr int FK = 16;       // columns per staged chunk
 constexpr int FP = FB + 16;  // LDS pitch of a staged chunk (bank spread, as trailing.hip)
 constexpr int CHAIN = 2;     // blocks below the diagonal that count as the chain's
+constexpr bool LEAVE = FLOW_LEAVE;  // the including file's form, see FLOW_LONG
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 struct FlowProb {
@@ -127,18 +128,31 @@ struct CuClaim {
 };
 
 // Waits until min(*a, *b) >= want and returns it; -1 when the factorisation
-// has failed (info, if not NULL).  Called by every thread; one polls.
+// has failed (info, if not NULL).  Called by every thread; one polls.  Where
+// workgroups leave, those that come after a failure look at info first: a block
+// would otherwise sum all that is final before it meets a word that will not come
+// (n = 40,000 failing at column 20,000: 247 ms, with the look 158).
 __device__ __forceinline__ int await(const int *a, const int *b, int want, const int64_t *info, FlowShared &sh)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
         int x;
-        while ((x = min(peek(a), peek(b))) < want) {
-            if (info && peek(info) != 0) {
-                x = -1;
-                break;
+        if constexpr (LEAVE) {
+            for (;;) {
+                const int64_t failed = info ? peek(info) : 0;
+                x = min(peek(a), peek(b));
+                if (failed != 0) x = -1;
+                if (failed != 0 || x >= want) break;
+                __builtin_amdgcn_s_sleep(1);
             }
-            __builtin_amdgcn_s_sleep(1);
+        } else {
+            while ((x = min(peek(a), peek(b))) < want) {
+                if (info && peek(info) != 0) {
+                    x = -1;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         sh.word = x;
@@ -645,7 +659,6 @@ __device__ __forceinline__ void flow_pad(double *dinv, int j)
 // of the diagonal block's code the generator drives out depends on where both lie.
 // n = 8,100 takes 3.65 ms with it in the cache, 3.9 in part, 4.4 without (the first
 // call); beside the other form in one code object it was 3.9.
-constexpr bool LEAVE = FLOW_LEAVE;  // the including file's form
 constexpr double FLOW_LONG = 0.35e12;
 constexpr int FLOW_TURNS = 2;
 static unsigned flow_grid(int64_t tasks)

@@ -6,6 +6,7 @@ missing for the others, and every workspace held another θ's values before.
 Σ fails through sixty repeated locations, whose pivots come out as rounding
 noise of either sign (a single repeat would leave it to one rounding)."""
 import math
+import time
 
 import numpy as np
 import pytest
@@ -102,3 +103,21 @@ def test_independent_blocks_report_the_first_failing_block(g, ctx):
     ref = g.loglik_eval(ctx, *parts[0], THETA, g.gl_opts_default(tile=128))
     assert ref["status"] == g.GL_NOT_SPD and 6000 < ref["info"] <= 6000 + DUP
     assert (r["status"], r["info"]) == (g.GL_NOT_SPD, ref["info"])
+
+
+def test_failure_half_way_ends_the_evaluation(g, ctx):
+    """The blocks before column n/2 are half of the work: a failure there leaves the
+    other half out (the sums of the blocks after it would be a quarter more)."""
+    n = 40000
+    times = []
+    for bad in (None, n // 2):
+        x, y, z = field(n, 50, bad=bad)
+        for _ in range(2):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            r = g.loglik_eval(ctx, x, y, z, THETA)
+            t = time.perf_counter() - t0
+        times.append(t)
+    assert r["status"] == g.GL_NOT_SPD and n // 2 < r["info"] <= n // 2 + DUP
+    print(f"healthy {times[0]:.4f} s, failing {times[1]:.4f} s", flush=True)
+    assert times[1] < 0.65 * times[0]
