@@ -121,13 +121,14 @@ constexpr int TICK_B = 256;     // tile size of the batched engine
 constexpr int TICK_RING = 4;    // descriptor buffers
 constexpr int TICK_DEPTH = 2;   // ticks in flight
 constexpr int TICK_MAX = 64;    // residents per tick
-// Work of a tick beyond one request: that of five of n = 16,500, about 110 ms, a
+// Work of a tick beyond one request: that of four of n = 16,500, about 100 ms, a
 // result's and a workspace's longest stay.  TICK_SHORT: up to here one request
 // leaves most of the chip idle.  A request of 1,000 points with 15 of 16,000 takes
-// 1.1 ms (170 to 320 in their ticks); 64 optimisers on 1,000 to 16,000 points are
-// served 164 evaluations/s, median latency 379 ms (159 and 411 with everything in
-// common ticks; 165, 388 and a shorter tail with 6e12).
-constexpr double TICK_FLOPS = 8e12;
+// 1.1 ms (170 to 320 in their ticks).  64 optimisers on 1,000 to 16,000 points,
+// evaluations/s, median and 99 % latency: 165, 357, 485 ms (161, 406, 490 with
+// everything in common ticks); 5e12 164, 349, 450, 6e12 165, 388, 427, but then
+// 16 requests at once take 122-123 ms instead of 119.6; 8e12 166, 379, 494.
+constexpr double TICK_FLOPS = 7e12;
 constexpr int64_t TICK_SHORT = 4096;
 
 struct Resident {

@@ -4,7 +4,7 @@
 // while the gate is shut, so nothing the queue has launched ends: what it has
 // launched, what still waits and what can be cancelled is then fixed.
 //
-// Sixteen requests of n = 16,384 (five to a launch) and two of n = 700 after them:
+// Sixteen requests of n = 16,384 (four to a launch) and two of n = 700 after them:
 // two launches of long requests, the first of which may have taken whatever had
 // arrived, then two of short ones; the other long requests wait, and those can be
 // cancelled, the launched ones cannot.  Prints "ok" when everything holds.
