@@ -23,7 +23,7 @@ struct BatchReq {
     int32_t *words;              // flow_words() ints, cleared with the staging
 };
 
-// Progress words of one whole factorisation (flow.hip): a ticket and three words
+// Progress words of one whole factorisation (flow.hpp): a ticket and three words
 // per 128-column block, each on a cache line of its own from one block on.
 __host__ __device__ inline int flow_stride(int64_t n) { return n >= 128 ? 16 : 1; }
 __host__ __device__ inline int64_t flow_words(int64_t n, int stride) { return (2 + 3 * ((n + 127) / 128)) * stride; }

@@ -118,11 +118,11 @@ bool valid_theta_for(const gl_theta &t, const gl_opts &o);
 size_t work_bytes(int64_t n, int b, int precision);
 // first_done: the POTRF of tile 0 has already run (logsum[0], dinv of step 0).
 int factorize(Lanes &ln, Work &w, hipStream_t s, bool solve, int64_t near, bool first_done = false);
-// The same in one launch (flow.hip): every block of L computed start to end by
+// The same in one launch (flow.hpp): every block of L computed start to end by
 // one workgroup, the same operations in the same order, so the same bits as
 // factorize().  Not part of builds without device code (weak).
 int flow_factorize(Work &w, hipStream_t s, bool solve) __attribute__((weak));
-// Kriging variances of m new locations from a finished factor (flow.hip, weak
+// Kriging variances of m new locations from a finished factor (flow.hpp, weak
 // too): st holds the right-hand sides (launch_gen_rhs) and scratch
 // flow_rhs_scratch(n, m) doubles.
 int64_t flow_rhs_scratch(int64_t n, int64_t m) __attribute__((weak));
@@ -140,8 +140,8 @@ int solve_join(Lanes &ln, hipStream_t s);
 // Tiles updated one panel at a time at even steps (gl_opts.near_tiles; 0:
 // b tiles, about 2.6 ms of binary64 update at tile 512).
 int64_t near_tiles_for(int b, int32_t requested);
-// Enqueue a whole evaluation on s (inputs already in w.x, w.y, w.v) and the
-// copy of its scalar results to out_h; does not wait.
+// Enqueue a whole evaluation on s (inputs already in w.x, w.y, w.v), whose last
+// kernel writes the scalar results to out_h (pinned); does not wait.
 int eval_launch(Lanes &ln, Work &w, gl_theta th, const gl_opts &o, hipStream_t s, DevResult *out_h,
                 MixedPlan *plan_out = nullptr);
 // Copy n inputs into the padded workspace vectors, in Morton order when

@@ -45,13 +45,14 @@
 // (potrf.hip, trsm.hip, trailing.hip, solve.hip), so both give the same bits.
 //
 // Bound by the matrix cores from about n = 12,000 up (69 TFLOP/s of 78.6 at
-// n = 40,000 and 100,000) and by the chain below: 36.5 µs per 128 columns, of
-// which the two 64×64 factors take 16, the panel and update between them 5.7,
-// L_j+1,j 4.5 after the second half of L_jj and the last 64 columns of the next
-// diagonal block 7 (46.6 before the claims, the early halves and the forward
-// solve off the chain; then 71 at n = 8,100 where it shared the CUs, 55 now).
-// Whole evaluations, step schedule and this: n = 400 480 and 185 µs, n = 1,600
-// 1.49 and 0.51 ms, n = 8,100 11.2 and 3.9 ms, n = 40,000 373 and 309 ms.
+// n = 40,000 and 100,000) and by the chain below: 36.5 µs per 128 columns at
+// n = 1,600, of which the two 64×64 factors take 16, the panel and update between
+// them 5.7, L_j+1,j 4.5 after the second half of L_jj and the last 64 columns of
+// the next diagonal block 7 (46.6 before the claims, the early halves and the
+// forward solve off the chain).  At n = 8,100, where the chain shares the CUs with
+// the other blocks, a step takes 55 µs (71 before).  Whole evaluations, step
+// schedule and this: n = 400 480 and 164 µs, n = 1,600 1.49 and 0.49 ms, n = 8,100
+// 11.2 and 3.8 ms, n = 40,000 371 and 311 ms.
 #pragma once
 
 #include <algorithm>
@@ -654,11 +655,11 @@ __device__ __forceinline__ void flow_pad(double *dinv, int j)
 // evaluation itself takes 314 ms either way.  (Without workgroups to spare it takes
 // 333: they are dealt to the XCDs in turn, and an XCD that is ahead runs out of its
 // share.  Those left over find no ticket.)
-// The two forms are compiled apart: a kernel's 60 KB and the code of the generator
-// before it do not fit the instruction cache (64 KB for two CUs) together, so how much
-// of the diagonal block's code the generator drives out depends on where both lie.
-// n = 8,100 takes 3.65 ms with it in the cache, 3.9 in part, 4.4 without (the first
-// call); beside the other form in one code object it was 3.9.
+// The two forms are compiled apart, so that the code of the one that stays keeps
+// its place: with both in one code object n = 8,100 took 4.1 ms instead of 3.85
+// (3.9 and 3.64 in the kernel) by the same instructions 256 bytes further on, after
+// some generator kernels and not after others.  What does it is not known
+// (instruction cache misses are few, 3e-5 of the requests, also on a first call).
 constexpr double FLOW_LONG = 0.35e12;
 constexpr int FLOW_TURNS = 2;
 static unsigned flow_grid(int64_t tasks)
