@@ -89,12 +89,22 @@ def test_small_request_beside_a_batch_of_large_ones(g, ctx, delay):
 
 
 def test_kernel_of_another_stream_runs_beside_a_large_evaluation(g, ctx):
+    """The first of several streams' kernels to end: a stream may share the
+    evaluation's hardware queue (a process has four), others then do not."""
     x, y, z = field(LARGE, 52)
     a = torch.ones(1 << 20, device="cuda")
-    side = torch.cuda.Stream()
+    sides = [torch.cuda.Stream() for _ in range(6)]
+
+    def launch(factor):
+        out = []
+        for s in sides:
+            with torch.cuda.stream(s):
+                out.append((a * factor, torch.cuda.Event()))
+                out[-1][1].record()
+        return out
+
     g.loglik_eval(ctx, x, y, z, THETA)
-    with torch.cuda.stream(side):
-        b = a * 2
+    launch(2)
     torch.cuda.synchronize()
     took = []
 
@@ -107,11 +117,12 @@ def test_kernel_of_another_stream_runs_beside_a_large_evaluation(g, ctx):
     th.start()
     time.sleep(0.02)
     t1 = time.perf_counter()
-    with torch.cuda.stream(side):
-        b = a * 3
-    side.synchronize()
+    launched = launch(3)
+    while not any(e.query() for _, e in launched):
+        time.sleep(1e-4)
     t2 = time.perf_counter()
     th.join()
+    torch.cuda.synchronize()
     print(f"kernel {t2 - t1:.4f} s, evaluation {took[0]:.4f} s", flush=True)
-    assert float(b[0]) == 3.0
+    assert all(float(b[0]) == 3.0 for b, _ in launched)
     assert t2 - t1 < 0.5 * took[0]
